@@ -913,18 +913,6 @@ struct BlockPlan {
   bool valid = false;             // the block has a chunk
 };
 
-// Inclusive prefix sum over the 64 lanes of a wavefront (DPP row shifts,
-// then the row broadcasts of lanes 15 and 31).
-__device__ inline int wave_incl_scan_i32(int v) {
-  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);  // row_shr:1
-  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);  // row_shr:2
-  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);  // row_shr:4
-  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);  // row_shr:8
-  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);  // row_bcast:15
-  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);  // row_bcast:31
-  return v;
-}
-
 // Hinted steps are capped so that their sum over 1024 sequences stays an int.
 constexpr int kMaxHintSteps = 1 << 20;
 

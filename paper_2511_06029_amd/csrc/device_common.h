@@ -98,6 +98,18 @@ __device__ inline double wave_sum_d(double v) {
   return v;
 }
 
+// Inclusive prefix sum over the 64 lanes of a wavefront (DPP row shifts,
+// then the row broadcasts of lanes 15 and 31).
+__device__ inline int wave_incl_scan_i32(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);  // row_shr:1
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);  // row_shr:2
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);  // row_shr:4
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);  // row_shr:8
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);  // row_bcast:15
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);  // row_bcast:31
+  return v;
+}
+
 // Inclusive scan of an int64 over one wave.
 __device__ inline long long wave_incl_scan(long long v) {
   const int lane = threadIdx.x & (kWave - 1);

@@ -3,22 +3,25 @@
 //
 // The qlen newest rows of each (sequence, KV head) segment come with queries;
 // query i sits at position p = n - qlen + i and attends rows 0 .. p.  Two
-// launches:
+// launches, both on v_mfma_f32_32x32x16_bf16:
 //
-//  1. prefill_fwd_kernel: flash attention forward.  A block holds 32 query
-//     positions of one KV group and up to four of its query heads (one head
-//     per wavefront) and walks the keys in 32-row steps, K and V tiles shared
-//     by the waves through LDS (direct loads, double buffered).  S^T = K Q^T
-//     on the matrix cores (v_mfma_f32_16x16x32_bf16), online softmax in base
-//     2 with one query per lane column, O^T = V^T P^T with P split into bf16
-//     high and low parts for fp32-level accuracy.  Writes out and each
-//     query's final (max, 1 / sum).
-//  2. prefill_score_kernel: key-major.  A block owns 256 keys (64 per wave,
-//     K in registers) and walks every later query tile of every head of the
-//     group, recomputing S^T and summing exp2(x - max) / sum over the
-//     queries; each key's total is added to its score once, so there are no
-//     atomics and the result does not depend on scheduling.
+//  1. prefill_fwd_kernel: flash attention forward.  A wavefront's unit is 32
+//     query positions of one head; a block holds four consecutive units of a
+//     KV group (ordered by position, then head) and walks the keys in 64-row
+//     steps, K and V tiles shared by the waves through LDS (direct loads,
+//     double buffered).  S^T = K Q^T, online softmax in base 2 with one query
+//     per lane column, O^T = V^T P^T with P split into bf16 high and low
+//     parts for fp32-level accuracy.  Writes out and each query's final
+//     (max, 1 / sum).
+//  2. prefill_score_kernel: key-major.  A wavefront keeps its keys in
+//     registers and walks every later query tile of every head of the group,
+//     recomputing S^T and summing exp2(x - max) / sum over the queries.
+//     The query tiles go round robin to the block's item groups, whose sums
+//     are added in order, and each key's total is added to its score once, so
+//     there are no atomics and the result does not depend on scheduling.
 #include <math.h>
+
+#include <type_traits>
 
 #include "device_common.h"
 #include "lethe_internal.h"
@@ -33,7 +36,9 @@ constexpr float kPfNegBig = -1.0e30f;
 
 typedef __bf16 pf_bf16x8_t __attribute__((ext_vector_type(8)));
 typedef __bf16 pf_bf16x4_t __attribute__((ext_vector_type(4)));
-typedef float pf_f32x4_t __attribute__((ext_vector_type(4)));
+typedef __bf16 pf_bf16x2_t __attribute__((ext_vector_type(2)));
+typedef float pf_f32x2_t __attribute__((ext_vector_type(2)));
+typedef float pf_f32x16_t __attribute__((ext_vector_type(16)));
 typedef __attribute__((address_space(3))) pf_bf16x4_t pf_lds_bf16x4_t;
 typedef __attribute__((address_space(3))) char pf_lds_char_t;
 typedef __attribute__((address_space(3))) void pf_lds_void_t;
@@ -41,22 +46,23 @@ typedef __attribute__((address_space(1))) const void pf_global_cvoid_t;
 
 template <int D>
 struct PfCfg {
-  static constexpr int KK = D / 32;          // k-steps of 32 over the head dim
-  static constexpr int NT = D / 16;          // output tiles of 16 dims
+  static constexpr int KS = D / 16;          // k-steps of 16 over the head dim
+  static constexpr int NT = D / 32;          // output tiles of 32 dims
   static constexpr int ROWB = D * 2;         // bytes per bf16 row
   static constexpr int CH = ROWB / 16;       // 16-byte chunks per row
-  static constexpr int STEP = 32;            // key rows per step
+  static constexpr int STEP = 64;            // key rows per step
   // K / Q tiles: chunk c of row r at 16-byte slot r CH + (c ^ (r mod CH)), so
   // the 16 rows an operand read touches fall in different LDS banks.
   static constexpr int KTILE = STEP * ROWB;
+  static constexpr int KLOADS = KTILE / (kWave * 16);
   static __device__ constexpr int kslot(int r, int c) { return r * CH + (c ^ (r % CH)); }
   // V tiles: load u (one wavefront, 16 bytes a lane) carries rows
-  // u + VLOADS j; blocks of 1 KB + 32 bytes keep the rows of one transposing
-  // read 8 banks apart.
+  // u + VLOADS j into block u; the blocks' padding spreads the rows of one
+  // transposing read over the LDS banks.
   static constexpr int LPR = ROWB / 16;
   static constexpr int RPL = kWave / LPR;
   static constexpr int VLOADS = STEP / RPL;
-  static constexpr int VBLK = kWave * 16 + 32;
+  static constexpr int VBLK = kWave * 16 + 64;
   static constexpr int VTILE = VLOADS * VBLK;
   static __device__ constexpr int vaddr(int r, int c) { return (r % VLOADS) * VBLK + (r / VLOADS) * ROWB + c; }
   static constexpr int BUF = KTILE + VTILE;
@@ -69,46 +75,23 @@ __device__ inline void wait_vmcnt() {
   __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
 }
 
-// Transposing 64-bit LDS read of four bf16 values.  Written as inline
-// assembly so that the compiler does not order it after every outstanding
-// direct-to-LDS load (it cannot tell which buffer those fill).  The compiler
-// does not track these reads either: lgkm_fence() must run before the
-// results are used.
-__device__ inline pf_bf16x4_t lds_read_tr(const pf_lds_char_t* p) {
-  typedef unsigned u32x2_t __attribute__((ext_vector_type(2)));
-  u32x2_t r;
-  const unsigned addr = (unsigned)(unsigned long)p;
-  asm volatile("ds_read_b64_tr_b16 %0, %1" : "=v"(r) : "v"(addr));
-  return __builtin_bit_cast(pf_bf16x4_t, r);
-}
-
-// Waits for every outstanding LDS read.  The operands tie the wait to the
-// registers those reads fill, so no use of them can be scheduled before it.
-template <int NT>
-__device__ inline void lgkm_fence(pf_bf16x8_t (&v)[NT]) {
-  static_assert(NT == 4 || NT == 8, "operand tiles");
-  if constexpr (NT == 4) {
-    asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]));
-  } else {
-    asm volatile("s_waitcnt lgkmcnt(0)"
-                 : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]), "+v"(v[5]), "+v"(v[6]), "+v"(v[7]));
-  }
-}
-
-// 64-bit LDS read that waits for its own result (same reason as lds_read_tr).
-__device__ inline float2 lds_read_f2(const pf_lds_char_t* p) {
-  typedef float f32x2_t __attribute__((ext_vector_type(2)));
-  f32x2_t r;
-  const unsigned addr = (unsigned)(unsigned long)p;
-  asm volatile("ds_read_b64 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=v"(r) : "v"(addr));
-  return make_float2(r[0], r[1]);
-}
-
 __device__ inline pf_bf16x8_t pf_zero8() {
   pf_bf16x8_t z;
 #pragma unroll
   for (int j = 0; j < 8; ++j) z[j] = (__bf16)0.0f;
   return z;
+}
+
+// 16 bytes a lane from `base + off` (base wave-uniform) into LDS: lane l's
+// land at dst + 16 l.
+__device__ inline void pf_load_lds(const char* base, unsigned off, pf_lds_char_t* dst) {
+  __builtin_amdgcn_global_load_lds((pf_global_cvoid_t*)(base + off), (pf_lds_void_t*)dst, 16, 0, 0);
+}
+
+// The larger of v and the other 32-lane half's.
+__device__ inline float pf_max_halves(float v) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
 
 // Sizes of one sequence, or false (flagged) when they do not fit together.
@@ -136,401 +119,510 @@ __device__ inline bool pf_seq(const PrefillArgs& a, int b, int h, PfSeq& sq) {
 // ---------------------------------------------------------------------------
 // Pass 1: outputs and per-query softmax statistics.
 // ---------------------------------------------------------------------------
+// Bound by the matrix cores at the clock the power limit leaves them: at
+// batch 8, 2048 tokens, Llama-8B heads, both passes do 550 GFLOP (P V in two
+// halves, S^T again in pass 2) in 0.61 ms, 0.90 PFLOP/s, where an 8192^3 bf16
+// library product reaches 1.13 to 1.23 on the same data distribution (zeros
+// in place of the data: 0.50 ms and 1.70).  16x16x32 products with 32-key
+// steps took 0.81 ms: twice the LDS reads and softmax instructions a flop,
+// and a tile's four waves idled where a group has fewer heads.  The V blocks'
+// 64 bytes of padding make its reads free of bank conflicts (32 bytes: a
+// third of the LDS cycles); two blocks of up to 256 registers a lane fit a CU.
 template <int D, int G>
 __global__ __launch_bounds__(kPfThreads) __attribute__((amdgpu_waves_per_eu(2))) void prefill_fwd_kernel(PrefillArgs a) {
   using Cfg = PfCfg<D>;
-  constexpr int KK = Cfg::KK, NT = Cfg::NT, ROWB = Cfg::ROWB, CH = Cfg::CH;
-  constexpr int NQUAD = (G + 3) / 4;
-  constexpr int NBUF = 3;  // tiles st, st + 1 and st + 2 in flight
-  constexpr int KLOADS = Cfg::KTILE / (kWave * 16);
-  constexpr int LPW = (KLOADS + Cfg::VLOADS) / kPfWaves;  // direct loads per wave and step
-  static_assert((KLOADS + Cfg::VLOADS) % kPfWaves == 0, "loads split evenly over the waves");
-  __shared__ __attribute__((aligned(16))) char tiles[NBUF][Cfg::BUF];
+  constexpr int KS = Cfg::KS, NT = Cfg::NT, ROWB = Cfg::ROWB, CH = Cfg::CH, STEP = Cfg::STEP;
+  static_assert(Cfg::KLOADS % kPfWaves == 0 && Cfg::VLOADS % kPfWaves == 0, "loads split evenly over the waves");
+  constexpr int KPW = Cfg::KLOADS / kPfWaves, VPW = Cfg::VLOADS / kPfWaves;  // loads per wave and step
+  // Separate arrays, so that the compiler can tell a read of one tile from
+  // the direct loads that fill another.
+  __shared__ __attribute__((aligned(16))) char ktile0[Cfg::KTILE];
+  __shared__ __attribute__((aligned(16))) char ktile1[Cfg::KTILE];
+  __shared__ __attribute__((aligned(16))) char vtile0[Cfg::VTILE];
+  __shared__ __attribute__((aligned(16))) char vtile1[Cfg::VTILE];
 
   const int tid = threadIdx.x;
   const int lane = tid & (kWave - 1);
-  const int w = tid / kWave;
-  const int g4 = lane >> 4;
-  const int s = lane & 15;
-  const int ntiles = (a.max_q + 31) / 32;
-  int idx = blockIdx.x;
-  const int quad = idx % NQUAD;
-  idx /= NQUAD;
-  const int seg = idx % (a.B * a.HK);
-  const int pt = ntiles - 1 - idx / (a.B * a.HK);  // longest rows first
+  const int w = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const int hh = lane >> 5;  // lane half
+  const int s = lane & 31;   // query column
+  const int segs = a.B * a.HK;
+  const int nub = ((a.max_q + 31) / 32 * G + kPfWaves - 1) / kPfWaves;
+  const int seg = blockIdx.x % segs;
+  const int ub = nub - 1 - (int)(blockIdx.x / segs);  // longest rows first
   const int b = seg / a.HK, h = seg % a.HK;
   PfSeq sq;
   if (!pf_seq(a, b, h, sq)) {
-    if (tid == 0 && pt == 0 && quad == 0) atomicOr(a.dev_status, LETHE_DEV_BAD_LAYOUT);
+    if (tid == 0 && ub == 0) atomicOr(a.dev_status, LETHE_DEV_BAD_LAYOUT);
     return;
   }
-  if (32 * pt >= sq.qlen) return;
+  const int live = (sq.qlen + 31) / 32;  // tiles with a query
+  if (kPfWaves * ub >= live * G) return;
   const int HQ = a.HK * G;
-  const int g = 4 * quad + w;
-  const bool active = g < G;  // wave-uniform
+  const int unit = kPfWaves * ub + w;
+  const int pt = unit / G, g = unit % G;
+  const bool active = pt < live;  // wave-uniform
   const int p0 = sq.first + 32 * pt;
-  const int kend = min(sq.n, p0 + 32);
-  const int nsteps = (kend + Cfg::STEP - 1) / Cfg::STEP;
+  const int kend = active ? min(sq.n, p0 + 32) : 0;  // keys of this wave
+  const int tlast = min((kPfWaves * ub + kPfWaves - 1) / G, live - 1);
+  const int kend_blk = min(sq.n, sq.first + 32 * tlast + 32);
+  const int nsteps = (kend_blk + STEP - 1) / STEP;
   const char* Kb = reinterpret_cast<const char*>(a.k) + sq.row0 * ROWB;
   const char* Vb = reinterpret_cast<const char*>(a.v) + sq.row0 * ROWB;
   const float sc = a.scale_log2;
 
-  // Queries of this wave's head as the B operand of S^T = K Q^T: lane (g4, s)
-  // of tile qt holds Q[query 32 pt + 16 qt + s][dims 32 kk + 8 g4 ..].
-  pf_bf16x8_t qb[2][KK];
-#pragma unroll
-  for (int qt = 0; qt < 2; ++qt) {
-    const int i = 32 * pt + 16 * qt + s;
+  // Queries of this wave's head as the B operand of S^T = K Q^T: lane (hh, s)
+  // holds Q[query 32 pt + s][dims 16 kk + 8 hh ..].
+  pf_bf16x8_t qb[KS];
+  {
+    const int i = 32 * pt + s;
     const char* qrow = reinterpret_cast<const char*>(a.q) + ((sq.q0 + i) * HQ + (long long)h * G + g) * ROWB;
 #pragma unroll
-    for (int kk = 0; kk < KK; ++kk)
-      qb[qt][kk] = (active && i < sq.qlen) ? *reinterpret_cast<const pf_bf16x8_t*>(qrow + 64 * kk + 16 * g4)
-                                           : pf_zero8();
+    for (int kk = 0; kk < KS; ++kk)
+      qb[kk] = (active && i < sq.qlen) ? *reinterpret_cast<const pf_bf16x8_t*>(qrow + 32 * kk + 16 * hh) : pf_zero8();
   }
 
-  auto issue = [&](int st, int buf) {
-    const int j0 = st * Cfg::STEP;
-    char* kt = tiles[buf];
-    char* vt = tiles[buf] + Cfg::KTILE;
+  // This wave's share of a step's tiles: K loads w, w + 4, ... and V loads
+  // likewise; the rows of consecutive shares are a constant apart, so one
+  // lane offset serves them all.  Rows past the last key of the block (final
+  // step only) read that key instead.
+  const int krow = (kWave * w + lane) / CH;  // + 256 / CH per load
+  const unsigned koff = krow * ROWB + 16 * ((lane % CH) ^ (krow % CH));
+  const int vrow = w + Cfg::VLOADS * (lane / Cfg::LPR);  // + kPfWaves per load
+  const unsigned voff = vrow * ROWB + 16 * (lane % Cfg::LPR);
+  auto issue_k = [&](int st, char* tile) {
+    const int j0 = st * STEP;
+    if (j0 >= kend_blk) return;
+    const char* kt = Kb + (long long)j0 * ROWB;
+    pf_lds_char_t* kl = (pf_lds_char_t*)tile + kWave * 16 * w;
+    if (j0 + STEP <= kend_blk) {
 #pragma unroll
-    for (int t = w; t < KLOADS + Cfg::VLOADS; t += kPfWaves) {
-      if (t < KLOADS) {
-        const int q = kWave * t + lane;
-        const int r = q / CH, c = (q % CH) ^ (r % CH);
-        const int row = min(j0 + r, kend - 1);
-        __builtin_amdgcn_global_load_lds((pf_global_cvoid_t*)(Kb + (long long)row * ROWB + 16 * c),
-                                         (pf_lds_void_t*)((pf_lds_char_t*)kt + kWave * 16 * t), 16, 0, 0);
-      } else {
-        const int u = t - KLOADS;
-        const int row = min(j0 + u + Cfg::VLOADS * (lane / Cfg::LPR), kend - 1);
-        __builtin_amdgcn_global_load_lds((pf_global_cvoid_t*)(Vb + (long long)row * ROWB + 16 * (lane % Cfg::LPR)),
-                                         (pf_lds_void_t*)((pf_lds_char_t*)vt + u * Cfg::VBLK), 16, 0, 0);
-      }
+      for (int k = 0; k < KPW; ++k)
+        pf_load_lds(kt + k * (kPfThreads / CH) * ROWB, koff, kl + kWave * 16 * kPfWaves * k);
+    } else {
+      const int last = kend_blk - 1 - j0;
+#pragma unroll
+      for (int k = 0; k < KPW; ++k)
+        pf_load_lds(kt, min(krow + k * (kPfThreads / CH), last) * ROWB + 16 * ((lane % CH) ^ (krow % CH)),
+                    kl + kWave * 16 * kPfWaves * k);
+    }
+  };
+  auto issue_v = [&](int st, char* tile) {
+    const int j0 = st * STEP;
+    if (j0 >= kend_blk) return;
+    const char* vt = Vb + (long long)j0 * ROWB;
+    pf_lds_char_t* vl = (pf_lds_char_t*)tile + Cfg::VBLK * w;
+    if (j0 + STEP <= kend_blk) {
+#pragma unroll
+      for (int k = 0; k < VPW; ++k) pf_load_lds(vt + k * kPfWaves * ROWB, voff, vl + Cfg::VBLK * kPfWaves * k);
+    } else {
+      const int last = kend_blk - 1 - j0;
+#pragma unroll
+      for (int k = 0; k < VPW; ++k)
+        pf_load_lds(vt, min(vrow + k * kPfWaves, last) * ROWB + 16 * (lane % Cfg::LPR),
+                    vl + Cfg::VBLK * kPfWaves * k);
     }
   };
 
-  float m[2] = {kPfNegBig, kPfNegBig}, l[2] = {0.0f, 0.0f};
-  pf_f32x4_t o[NT][2];
+  const int pos = p0 + s;  // this lane's query position
+  float m = kPfNegBig, l = 0.0f, corr = 1.0f;
+  pf_f32x16_t o[NT];
 #pragma unroll
-  for (int nt = 0; nt < NT; ++nt) o[nt][0] = o[nt][1] = pf_f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
-
-  issue(0, 0);
-  if (nsteps > 1) issue(1, 1);
-  const int rsub = 4 * g4 + (s >> 2);
-  for (int st = 0; st < nsteps; ++st) {
-    // This wave's loads of tile st are done once at most the LPW loads of
-    // tile st + 1 are outstanding; the barrier makes every wave's visible
-    // and guarantees tile st - 1 has been read by all.
-    if (st + 1 < nsteps)
-      wait_vmcnt<LPW>();
-    else
-      wait_vmcnt<0>();
-    __syncthreads();
-    if (st + 2 < nsteps) issue(st + 2, (st + 2) % NBUF);
-    if (!active) continue;
-    const int j0 = st * Cfg::STEP;
-    const char* kt = tiles[st % NBUF];
-    const pf_lds_char_t* vt = (const pf_lds_char_t*)(tiles[st % NBUF] + Cfg::KTILE);
-    // V^T operands through the transposing LDS read: lane s of group g4
-    // points at row 4 g4 + s / 4 and 16 rows further, column 16 nt + 4 (s mod 4).
-    pf_bf16x8_t av[NT];
+  for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
-      const int col = (16 * nt + 4 * (s & 3)) * 2;
-      const pf_bf16x4_t a0 = lds_read_tr(vt + Cfg::vaddr(rsub, col));
-      const pf_bf16x4_t a1 = lds_read_tr(vt + Cfg::vaddr(rsub + 16, col));
-      av[nt] = __builtin_shufflevector(a0, a1, 0, 1, 2, 3, 4, 5, 6, 7);
-    }
-
-    pf_f32x4_t sacc[2][2];
+    for (int r = 0; r < 16; ++r) o[nt][r] = 0.0f;
+  // S^T of a step: lane (hh, s), register r of sub-tile T: key j0 + 32 T +
+  // 8 (r / 4) + 4 hh + r % 4, query s.
+  pf_f32x16_t sa[2], sb[2];
+  auto clear = [&](pf_f32x16_t (&x)[2]) {
+#pragma unroll
+    for (int T = 0; T < 2; ++T)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) x[T][r] = 0.0f;
+  };
+  auto qk = [&](pf_f32x16_t (&x)[2], const char* kt, int kk) {
 #pragma unroll
     for (int T = 0; T < 2; ++T) {
-      pf_bf16x8_t kr[KK];
-#pragma unroll
-      for (int kk = 0; kk < KK; ++kk)
-        kr[kk] = *reinterpret_cast<const pf_bf16x8_t*>(kt + 16 * Cfg::kslot(16 * T + s, 4 * kk + g4));
-#pragma unroll
-      for (int qt = 0; qt < 2; ++qt) {
-        sacc[T][qt] = pf_f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-        for (int kk = 0; kk < KK; ++kk)
-          sacc[T][qt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kr[kk], qb[qt][kk], sacc[T][qt], 0, 0, 0);
-      }
+      const pf_bf16x8_t kr = *reinterpret_cast<const pf_bf16x8_t*>(kt + 16 * Cfg::kslot(32 * T + s, 2 * kk + hh));
+      x[T] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kr, qb[kk], x[T], 0, 0, 0);
     }
-
-    // Softmax of query 16 qt + s over keys j0 + 16 T + 4 g4 + rr.  Steps
-    // wholly below the diagonal (every key precedes every query of the tile
-    // and is live) skip the mask.
-    const bool interior = j0 + Cfg::STEP - 1 <= p0 && j0 + Cfg::STEP <= kend;
-    pf_bf16x8_t ph[2], pl[2];
+  };
+  // Steps wholly below the diagonal (every key precedes every query of the
+  // unit and is live) skip the mask.
+  auto mask = [&](pf_f32x16_t (&x)[2], int j0) {
+    if (j0 + STEP - 1 > p0 || j0 + STEP > kend) {
+      asm volatile("");  // keeps the mask behind a branch
+      const int lim = min(pos, kend - 1) - j0 - 4 * hh;
 #pragma unroll
-    for (int qt = 0; qt < 2; ++qt) {
-      const int pos = p0 + 16 * qt + s;
-      float x[8];
-      float mx = kPfNegBig;
-      if (interior) {
+      for (int T = 0; T < 2; ++T)
 #pragma unroll
-        for (int jj = 0; jj < 8; ++jj) {
-          x[jj] = sacc[jj >> 2][qt][jj & 3] * sc;
-          mx = fmaxf(mx, x[jj]);
-        }
+        for (int r = 0; r < 16; ++r)
+          if (32 * T + 8 * (r >> 2) + (r & 3) > lim) x[T][r] = -INFINITY;
+    }
+  };
+  auto row_max = [&](const pf_f32x16_t (&x)[2]) {
+    float mx = fmaxf(x[0][0], x[1][0]);
+#pragma unroll
+    for (int r = 1; r < 16; ++r) mx = fmaxf(fmaxf(mx, x[0][r]), x[1][r]);
+    return mx;
+  };
+  // V^T operand of keys 16 mm .. + 15 and dims 32 nt .. through the
+  // transposing LDS read: lane i of a 16-lane group points at row 4 hh + i / 4
+  // (and 8 rows further), 4 columns from 32 nt + 16 (group mod 2) + 4 (i mod 4).
+  auto v_operand = [&](const char* vtile, int mm, int nt) {
+    const pf_lds_char_t* vt = (const pf_lds_char_t*)vtile;
+    const int vr = 16 * mm + 4 * hh + ((lane & 15) >> 2);
+    const int col = (32 * nt + 16 * ((lane >> 4) & 1) + 4 * (lane & 3)) * 2;
+    const pf_bf16x4_t a0 = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((pf_lds_bf16x4_t*)(vt + Cfg::vaddr(vr, col)));
+    const pf_bf16x4_t a1 = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((pf_lds_bf16x4_t*)(vt + Cfg::vaddr(vr + 8, col)));
+    return __builtin_shufflevector(a0, a1, 0, 1, 2, 3, 4, 5, 6, 7);
+  };
+  // Once the running maxima settle most steps leave every lane's correction
+  // at exactly 1; the wave then skips the rescale.
+  auto rescale = [&]() {
+    if (__any(corr != 1.0f)) {
+      l *= corr;
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) o[nt][r] *= corr;
+    }
+  };
+  auto new_max = [&](const pf_f32x16_t (&x)[2]) {
+    const float mnew = fmaxf(m, pf_max_halves(row_max(x)) * sc);
+    corr = hw_exp2(m - mnew);
+    m = mnew;
+  };
+  // P of 16 keys in bf16 high and low parts: registers 8 (mm % 2) .. of
+  // sub-tile mm / 2 are the B operand of those keys in the order (j < 4:
+  // 4 hh + j, else 8 + 4 hh + j - 4) that the V^T operand follows.
+  float psum[2] = {0.0f, 0.0f};
+  auto weights = [&](const pf_f32x16_t (&x)[2], int mm, pf_bf16x8_t& ph, pf_bf16x8_t& pl) {
+#pragma unroll
+    for (int j = 0; j < 8; j += 2) {
+      const float pa = hw_exp2(fmaf(x[mm >> 1][8 * (mm & 1) + j], sc, -m));
+      const float pb = hw_exp2(fmaf(x[mm >> 1][8 * (mm & 1) + j + 1], sc, -m));
+      psum[0] += pa;
+      psum[1] += pb;
+      const pf_bf16x2_t hi = __builtin_convertvector((pf_f32x2_t{pa, pb}), pf_bf16x2_t);
+      const unsigned hb = __builtin_bit_cast(unsigned, hi);
+      const pf_bf16x2_t lo = __builtin_convertvector(
+          (pf_f32x2_t{pa - __uint_as_float(hb << 16), pb - __uint_as_float(hb & 0xffff0000u)}), pf_bf16x2_t);
+      ph[j] = hi[0];
+      ph[j + 1] = hi[1];
+      pl[j] = lo[0];
+      pl[j + 1] = lo[1];
+    }
+  };
+  auto pv = [&](const char* vtile, int mm, const pf_bf16x8_t& ph, const pf_bf16x8_t& pl) {
+    pf_bf16x8_t av[NT];
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) av[nt] = v_operand(vtile, mm, nt);
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) o[nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[nt], ph, o[nt], 0, 0, 0);
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) o[nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[nt], pl, o[nt], 0, 0, 0);
+  };
+  // A step of this wave that is not its last: the softmax weights and P V of
+  // step st, whose S^T is in sx, interleaved with S^T of step st + 1 into sn
+  // (K runs one tile ahead of V), so that the matrix cores work on both
+  // products while the weights are formed.
+  auto body = [&](int st, pf_f32x16_t (&sx)[2], pf_f32x16_t (&sn)[2], const char* knext, const char* vcur) {
+    rescale();
+    clear(sn);
+    psum[0] = psum[1] = 0.0f;
+    pf_bf16x8_t ph, pl, nh, nl;
+    weights(sx, 0, ph, pl);
+#pragma unroll
+    for (int kk = 0; kk < KS / 4; ++kk) qk(sn, knext, kk);
+#pragma unroll
+    for (int mm = 1; mm < 4; ++mm) {
+      weights(sx, mm, nh, nl);
+#pragma unroll
+      for (int kk = mm * KS / 4; kk < (mm + 1) * KS / 4; ++kk) qk(sn, knext, kk);
+      pv(vcur, mm - 1, ph, pl);
+      ph = nh;
+      pl = nl;
+    }
+    l += psum[0] + psum[1];
+    mask(sn, (st + 1) * STEP);
+    pv(vcur, 3, ph, pl);
+    new_max(sn);
+  };
+  // This wave's last step.  Rows past its keys that another wave's tile
+  // brought in have weight 0, and count as 0 so that an infinity there stays
+  // out of the sum.
+  auto last_body = [&](int st, const pf_f32x16_t (&sx)[2], const char* vcur) {
+    rescale();
+    psum[0] = psum[1] = 0.0f;
+#pragma unroll
+    for (int mm = 0; mm < 4; ++mm) {
+      pf_bf16x8_t ph, pl;
+      weights(sx, mm, ph, pl);
+      if constexpr (G % kPfWaves == 0) {
+        pv(vcur, mm, ph, pl);
       } else {
 #pragma unroll
-        for (int jj = 0; jj < 8; ++jj) {
-          const int key = j0 + 16 * (jj >> 2) + 4 * g4 + (jj & 3);
-          x[jj] = (key <= pos && key < kend) ? sacc[jj >> 2][qt][jj & 3] * sc : -INFINITY;
-          mx = fmaxf(mx, x[jj]);
+        for (int nt = 0; nt < NT; ++nt) {
+          pf_bf16x8_t av = v_operand(vcur, mm, nt);
+#pragma unroll
+          for (int j = 0; j < 8; ++j)
+            if (st * STEP + 16 * mm + 4 * hh + 8 * (j >> 2) + (j & 3) >= kend) av[j] = (__bf16)0.0f;
+          o[nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, ph, o[nt], 0, 0, 0);
+          o[nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, pl, o[nt], 0, 0, 0);
         }
       }
-      mx = fmaxf(mx, __shfl_xor(mx, 16));
-      mx = fmaxf(mx, __shfl_xor(mx, 32));
-      const float mnew = fmaxf(m[qt], mx);
-      const float corr = hw_exp2(m[qt] - mnew);
-      float psum = 0.0f;
-#pragma unroll
-      for (int jj = 0; jj < 8; ++jj) {
-        const float p = hw_exp2(x[jj] - mnew);
-        psum += p;
-        const __bf16 hi = (__bf16)p;
-        ph[qt][jj] = hi;
-        pl[qt][jj] = (__bf16)(p - (float)hi);
-      }
-      l[qt] = l[qt] * corr + psum;
-      m[qt] = mnew;
-      // Once the running maxima settle most steps leave every lane's
-      // correction at exactly 1; the wave then skips the rescale.
-      if (__any(corr != 1.0f)) {
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) o[nt][qt] *= corr;
-      }
     }
+    l += psum[0] + psum[1];
+  };
 
-    // O^T += V^T P^T.
-    lgkm_fence<NT>(av);
+  // At step st, K of step st + 2 and V of step st + 1 are on their way into
+  // the buffers that step st - 1 has used.  Each wave waits for its own loads
+  // (the barrier alone would not); the barrier then makes every wave's visible
+  // and guarantees that the buffers to fill have been read by all.
+  auto advance = [&](int st, char* kfill, char* vfill) {
+    wait_vmcnt<0>();
+    __syncthreads();
+    issue_k(st + 2, kfill);
+    issue_v(st + 1, vfill);
+  };
+  issue_k(0, ktile0);
+  issue_k(1, ktile1);
+  issue_v(0, vtile0);
+  wait_vmcnt<0>();
+  __syncthreads();
+  const int own = (kend + STEP - 1) / STEP;  // steps of this wave
+  clear(sa);
+  if (active) {
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
-#pragma unroll
-      for (int qt = 0; qt < 2; ++qt) {
-        o[nt][qt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[nt], ph[qt], o[nt][qt], 0, 0, 0);
-        o[nt][qt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[nt], pl[qt], o[nt][qt], 0, 0, 0);
-      }
-    }
+    for (int kk = 0; kk < KS; ++kk) qk(sa, ktile0, kk);
+    mask(sa, 0);
+    new_max(sa);
   }
+  int st = 0;
+  for (; st + 2 < own; st += 2) {
+    advance(st, ktile0, vtile1);
+    body(st, sa, sb, ktile1, vtile0);
+    advance(st + 1, ktile1, vtile0);
+    body(st + 1, sb, sa, ktile0, vtile1);
+  }
+  if (st + 1 < own) {
+    advance(st, ktile0, vtile1);
+    body(st, sa, sb, ktile1, vtile0);
+    ++st;
+    sa[0] = sb[0];
+    sa[1] = sb[1];
+  }
+  if (active) {
+    advance(st, (st & 1) ? ktile1 : ktile0, (st & 1) ? vtile0 : vtile1);
+    last_body(st, sa, (st & 1) ? vtile1 : vtile0);
+    ++st;
+  }
+  for (; st < nsteps; ++st) advance(st, (st & 1) ? ktile1 : ktile0, (st & 1) ? vtile0 : vtile1);
   if (!active) return;
 
-  // l is split over the four lane groups of a query column; m is common.
+  // l is split over the two lane halves of a query column; m is common.
+  l += __shfl_xor(l, 32);
+  const int i = 32 * pt + s;
+  if (i >= sq.qlen) return;
+  const float inv = 1.0f / l;
+  float* orow = a.out + ((sq.q0 + i) * HQ + (long long)h * G + g) * D;
 #pragma unroll
-  for (int qt = 0; qt < 2; ++qt) {
-    float lt = l[qt];
-    lt += __shfl_xor(lt, 16);
-    lt += __shfl_xor(lt, 32);
-    const int i = 32 * pt + 16 * qt + s;
-    if (i >= sq.qlen) continue;
-    const float inv = 1.0f / lt;
-    const long long qrow = (sq.q0 + i) * HQ + (long long)h * G + g;
-    float* orow = a.out + qrow * D;
+  for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
-      const pf_f32x4_t v = o[nt][qt] * inv;
-      *reinterpret_cast<float4*>(orow + 16 * nt + 4 * g4) = make_float4(v[0], v[1], v[2], v[3]);
-    }
-    if (g4 == 0)
-      *reinterpret_cast<float2*>(a.stat + 2 * ((long long)(h * G + g) * a.q_rows + sq.q0 + i)) = make_float2(m[qt], inv);
-  }
+    for (int r = 0; r < 16; r += 4)
+      *reinterpret_cast<float4*>(orow + 32 * nt + 2 * r + 4 * hh) =
+          make_float4(o[nt][r] * inv, o[nt][r + 1] * inv, o[nt][r + 2] * inv, o[nt][r + 3] * inv);
+  if (hh == 0)
+    *reinterpret_cast<float2*>(a.stat + 2 * ((long long)(h * G + g) * a.q_rows + sq.q0 + i)) = make_float2(m, inv);
 }
 
 // ---------------------------------------------------------------------------
 // Pass 2: importance seeding, key-major.
 // ---------------------------------------------------------------------------
-constexpr int kPfKeysPerWave = 64;
-constexpr int kPfKeysPerBlock = kPfWaves * kPfKeysPerWave;
-constexpr int kPfItemQ = 32;  // queries of one head per work item
-
-template <int D, int G>
-__global__ __launch_bounds__(kPfThreads) void prefill_score_kernel(PrefillArgs a) {
+// A block is KW key waves of 32 NS keys each times IG item groups: group ig
+// takes the work items (tile of 32 queries, head) ig, ig + IG, ... and keeps
+// its own double-buffered query tile.  A weight costs a multiply-add, an exp2
+// and a multiply-add against 16 matrix-core cycles a lane, so the pass needs
+// waves to overlap the two: 32 keys a wave hold 112 registers, four waves a
+// SIMD, where 64 keys held 190.
+template <int D, int G, int NS, int KW, int IG>
+__global__ __launch_bounds__(kWave * KW * IG) __attribute__((amdgpu_waves_per_eu(KW * IG / 4))) void
+    prefill_score_kernel(PrefillArgs a) {
   using Cfg = PfCfg<D>;
-  constexpr int KK = Cfg::KK, ROWB = Cfg::ROWB, CH = Cfg::CH;
-  constexpr int QTILE = kPfItemQ * ROWB;
-  constexpr int STATB = kPfItemQ * 8;  // (max, 1 / sum) per query
-  constexpr int BUFB = QTILE + STATB;
-  constexpr int NBUF = 3;
+  constexpr int KS = Cfg::KS, ROWB = Cfg::ROWB, CH = Cfg::CH;
+  constexpr int QTILE = 32 * ROWB;
   constexpr int QLOADS = QTILE / (kWave * 16);
-  static_assert(QLOADS % kPfWaves == 0, "query loads split evenly over the waves");
-  constexpr int LPW = QLOADS / kPfWaves;  // plus one statistics load on wave 0
-  __shared__ __attribute__((aligned(16))) char bufs[NBUF][BUFB];
+  static_assert(QLOADS % KW == 0, "query loads split evenly over the group's waves");
+  constexpr int LPW = QLOADS / KW;
+  constexpr int KEYS = 32 * NS * KW;  // keys per block
+  __shared__ __attribute__((aligned(16))) char buf0[IG * QTILE];
+  __shared__ __attribute__((aligned(16))) char buf1[IG * QTILE];
+  __shared__ float sums[IG][KEYS];
 
   const int tid = threadIdx.x;
   const int lane = tid & (kWave - 1);
-  const int w = tid / kWave;
-  const int g4 = lane >> 4;
-  const int s = lane & 15;
-  const int seg = blockIdx.x % (a.B * a.HK);
-  const int kb = blockIdx.x / (a.B * a.HK);  // low keys (most queries) first
+  const int w = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const int kw = w % KW, ig = w / KW;
+  const int hh = lane >> 5;
+  const int s = lane & 31;
+  const int segs = a.B * a.HK;
+  const int seg = blockIdx.x % segs;
+  const int kb = blockIdx.x / segs;  // low keys (most queries) first
   const int b = seg / a.HK, h = seg % a.HK;
   PfSeq sq;
   if (!pf_seq(a, b, h, sq)) return;  // flagged by the forward pass
-  const int kblk0 = kPfKeysPerBlock * kb;
+  const int kblk0 = KEYS * kb;
   if (sq.qlen == 0 || kblk0 >= sq.n) return;
   const int HQ = a.HK * G;
-  const int j0w = kblk0 + kPfKeysPerWave * w;
+  const int j0w = kblk0 + 32 * NS * kw;
   const char* Kb = reinterpret_cast<const char*>(a.k) + sq.row0 * ROWB;
   const float sc = a.scale_log2;
 
-  // This wave's 64 keys as the A operand (row 16 T + s, dims 32 kk + 8 g4 ..).
-  pf_bf16x8_t kr[4][KK];
+  // This wave's keys as the A operand (row 32 T + s, dims 16 kk + 8 hh ..).
+  pf_bf16x8_t kr[NS][KS];
 #pragma unroll
-  for (int T = 0; T < 4; ++T) {
-    const int row = min(j0w + 16 * T + s, sq.n - 1);
+  for (int T = 0; T < NS; ++T) {
+    const int row = min(j0w + 32 * T + s, sq.n - 1);
 #pragma unroll
-    for (int kk = 0; kk < KK; ++kk)
-      kr[T][kk] = *reinterpret_cast<const pf_bf16x8_t*>(Kb + (long long)row * ROWB + 64 * kk + 16 * g4);
+    for (int kk = 0; kk < KS; ++kk)
+      kr[T][kk] = *reinterpret_cast<const pf_bf16x8_t*>(Kb + (long long)row * ROWB + 32 * kk + 16 * hh);
   }
 
   // Work items: (tile of 32 queries, head) for every tile holding a position
   // at or after the block's first key.
-  const int it0 = max(0, kblk0 - sq.first) / kPfItemQ;
-  const int nit = (sq.qlen + kPfItemQ - 1) / kPfItemQ - it0;
-  const int nitems = nit * G;
-  auto issue = [&](int item, int buf) {
+  const int it0 = max(0, kblk0 - sq.first) / 32;
+  const int nitems = ((sq.qlen + 31) / 32 - it0) * G;
+  const int qrow = (kWave * kw + lane) / CH;  // + 64 KW / CH per load
+  float2 st_next = make_float2(0.0f, 0.0f);
+  auto issue = [&](int item, char* buf) {
+    if (item >= nitems) return;
     const int it = it0 + item / G, g = item % G;
+    const char* src = reinterpret_cast<const char*>(a.q) + ((sq.q0 + 32 * it) * HQ + (long long)h * G + g) * ROWB;
+    const int last = sq.qlen - 1 - 32 * it;  // queries past it read it instead
 #pragma unroll
-    for (int t = w; t < QLOADS; t += kPfWaves) {
-      const int q = kWave * t + lane;
-      const int r = q / CH, c = (q % CH) ^ (r % CH);
-      const int i = min(kPfItemQ * it + r, sq.qlen - 1);
-      const char* src = reinterpret_cast<const char*>(a.q) + ((sq.q0 + i) * HQ + (long long)h * G + g) * ROWB + 16 * c;
-      __builtin_amdgcn_global_load_lds((pf_global_cvoid_t*)src,
-                                       (pf_lds_void_t*)((pf_lds_char_t*)bufs[buf] + kWave * 16 * t), 16, 0, 0);
+    for (int k = 0; k < LPW; ++k) {
+      const int r = qrow + k * (kWave * KW / CH);
+      const int c = (lane % CH) ^ (r % CH);
+      pf_load_lds(src, (unsigned)(min(r, last) * HQ) * ROWB + 16 * c,
+                  (pf_lds_char_t*)buf + ig * QTILE + kWave * 16 * (kw + KW * k));
     }
-    if (w == 0 && lane < kPfItemQ / 2) {
-      // Statistics of the item's queries: 32 x 8 bytes, two queries a lane.
-      // A pair may reach one entry past the live ones (the workspace has
-      // slack for it); those entries belong to masked queries.
-      const int i = min(kPfItemQ * it + 2 * lane, sq.qlen - 1);
-      const float* src = a.stat + 2 * ((long long)(h * G + g) * a.q_rows + sq.q0 + i);
-      __builtin_amdgcn_global_load_lds((pf_global_cvoid_t*)src, (pf_lds_void_t*)((pf_lds_char_t*)bufs[buf] + QTILE),
-                                       16, 0, 0);
+    st_next = *reinterpret_cast<const float2*>(
+        a.stat + 2 * ((long long)(h * G + g) * a.q_rows + sq.q0 + 32 * it + min(s, last)));
+  };
+
+  float acc[NS][16];
+#pragma unroll
+  for (int T = 0; T < NS; ++T)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[T][r] = 0.0f;
+
+  auto compute = [&](int item, const char* buf, float2 qs) {
+    if (item >= nitems || j0w >= sq.n) return;
+    const int it = it0 + item / G;
+    const int pos0 = sq.first + 32 * it;  // position of the tile's first query
+    if (pos0 + 31 < j0w) return;          // every query precedes this wave's keys
+    const char* qt = buf + ig * QTILE;
+    pf_bf16x8_t qv[KS];
+#pragma unroll
+    for (int kk = 0; kk < KS; ++kk)
+      qv[kk] = *reinterpret_cast<const pf_bf16x8_t*>(qt + 16 * Cfg::kslot(s, 2 * kk + hh));
+    pf_f32x16_t sacc[NS];
+#pragma unroll
+    for (int T = 0; T < NS; ++T) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) sacc[T][r] = 0.0f;
+#pragma unroll
+      for (int kk = 0; kk < KS; ++kk)
+        sacc[T] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kr[T][kk], qv[kk], sacc[T], 0, 0, 0);
+    }
+    // Tiles whose every query is live and follows every key skip the mask
+    // (a masked weight is left out, whatever its query's statistics hold).
+    if (j0w + 32 * NS - 1 > pos0 || 32 * (it + 1) > sq.qlen) {
+      const int lim = 32 * it + s < sq.qlen ? pos0 + s - j0w - 4 * hh : -1;
+#pragma unroll
+      for (int T = 0; T < NS; ++T)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const float p = hw_exp2(fmaf(sacc[T][r], sc, -qs.x)) * qs.y;
+          acc[T][r] += 32 * T + 8 * (r >> 2) + (r & 3) > lim ? 0.0f : p;
+        }
+    } else {
+#pragma unroll
+      for (int T = 0; T < NS; ++T)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[T][r] = fmaf(hw_exp2(fmaf(sacc[T][r], sc, -qs.x)), qs.y, acc[T][r]);
     }
   };
 
-  float acc[4][4];
-#pragma unroll
-  for (int T = 0; T < 4; ++T)
-#pragma unroll
-    for (int rr = 0; rr < 4; ++rr) acc[T][rr] = 0.0f;
-
-  if (nitems > 0) issue(0, 0);
-  if (nitems > 1) issue(1, 1);
-  for (int item = 0; item < nitems; ++item) {
-    if (item + 1 < nitems) {
-      if (w == 0)
-        wait_vmcnt<LPW + 1>();
-      else
-        wait_vmcnt<LPW>();
-    } else {
-      wait_vmcnt<0>();
-    }
+  issue(ig, buf0);
+  const int rounds = (nitems + IG - 1) / IG;
+  for (int x = 0; x < rounds; x += 2) {
+    wait_vmcnt<0>();
     __syncthreads();
-    if (item + 2 < nitems) issue(item + 2, (item + 2) % NBUF);
-    const int it = it0 + item / G;
-    const int pos0 = sq.first + kPfItemQ * it;  // position of the tile's first query
-    // Nothing to do when every query of the tile precedes this wave's keys.
-    if (pos0 + kPfItemQ - 1 < j0w || j0w >= sq.n) continue;
-    const char* qt = bufs[item % NBUF];
-    const float* stl = reinterpret_cast<const float*>(qt + QTILE);
-    // No masking when every key is live and precedes every (live) query.
-    const bool full = j0w + kPfKeysPerWave - 1 <= pos0 && kPfItemQ * (it + 1) <= sq.qlen &&
-                      j0w + kPfKeysPerWave <= sq.n;
-    constexpr int QH = kPfItemQ / 16;
-    // Both query halves' operands and statistics, then every MFMA of the
-    // item with the k-step outermost: QH * 4 independent accumulators.
-    pf_bf16x8_t qv[QH][KK];
-    float off[QH];
-#pragma unroll
-    for (int qh = 0; qh < QH; ++qh) {
-#pragma unroll
-      for (int kk = 0; kk < KK; ++kk)
-        qv[qh][kk] = *reinterpret_cast<const pf_bf16x8_t*>(qt + 16 * Cfg::kslot(16 * qh + s, 4 * kk + g4));
-      // exp2(x - max) / sum = exp2(x - (max + log2(sum))).
-      const float2 st = lds_read_f2((const pf_lds_char_t*)(stl + 2 * (16 * qh + s)));
-      off[qh] = st.x - __log2f(st.y);
-    }
-    pf_f32x4_t sacc[QH][4];
-#pragma unroll
-    for (int qh = 0; qh < QH; ++qh)
-#pragma unroll
-      for (int T = 0; T < 4; ++T) sacc[qh][T] = pf_f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-    for (int kk = 0; kk < KK; ++kk)
-#pragma unroll
-      for (int qh = 0; qh < QH; ++qh)
-#pragma unroll
-        for (int T = 0; T < 4; ++T)
-          sacc[qh][T] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kr[T][kk], qv[qh][kk], sacc[qh][T], 0, 0, 0);
-#pragma unroll
-    for (int qh = 0; qh < QH; ++qh) {
-      const int i = kPfItemQ * it + 16 * qh + s;
-      const int pos = sq.first + i;
-      const bool valid = i < sq.qlen;
-#pragma unroll
-      for (int T = 0; T < 4; ++T) {
-        if (full) {
-#pragma unroll
-          for (int rr = 0; rr < 4; ++rr) acc[T][rr] += hw_exp2(fmaf(sacc[qh][T][rr], sc, -off[qh]));
-        } else {
-#pragma unroll
-          for (int rr = 0; rr < 4; ++rr) {
-            const int key = j0w + 16 * T + 4 * g4 + rr;
-            const float p = hw_exp2(fmaf(sacc[qh][T][rr], sc, -off[qh]));
-            acc[T][rr] += (valid && key <= pos && key < sq.n) ? p : 0.0f;
-          }
-        }
-      }
-    }
+    float2 qs = st_next;
+    issue((x + 1) * IG + ig, buf1);
+    compute(x * IG + ig, buf0, qs);
+    if (x + 1 >= rounds) break;
+    wait_vmcnt<0>();
+    __syncthreads();
+    qs = st_next;
+    issue((x + 2) * IG + ig, buf0);
+    compute((x + 1) * IG + ig, buf1, qs);
   }
 
-  // Sum over the 16 query columns, then one add per key.
+  // Sum over the 32 query columns: each exchange halves the keys a lane
+  // holds, until lane s holds key register s / 2.
 #pragma unroll
-  for (int T = 0; T < 4; ++T) {
+  for (int T = 0; T < NS; ++T) {
 #pragma unroll
-    for (int rr = 0; rr < 4; ++rr) {
-      float v = acc[T][rr];
-      v += __shfl_xor(v, 1);
-      v += __shfl_xor(v, 2);
-      v += __shfl_xor(v, 4);
-      v += __shfl_xor(v, 8);
-      acc[T][rr] = v;
-    }
-  }
-  if (s == 0) {
-    float* sb = a.score + sq.row0;
+    for (int half = 8; half >= 1; half /= 2) {
+      const bool up = (s & (2 * half)) != 0;
 #pragma unroll
-    for (int T = 0; T < 4; ++T) {
-#pragma unroll
-      for (int rr = 0; rr < 4; ++rr) {
-        const int key = j0w + 16 * T + 4 * g4 + rr;
-        if (key < sq.n) sb[key] += acc[T][rr];
+      for (int r = 0; r < half; ++r) {
+        const float mine = up ? acc[T][r + half] : acc[T][r];
+        const float give = up ? acc[T][r] : acc[T][r + half];
+        acc[T][r] = mine + __shfl_xor(give, 2 * half);
       }
     }
+    const float v = acc[T][0] + __shfl_xor(acc[T][0], 1);
+    const int r = s >> 1;
+    if ((s & 1) == 0) sums[ig][32 * (NS * kw + T) + 8 * (r >> 2) + 4 * hh + (r & 3)] = v;
   }
+  __syncthreads();
+  for (int j = tid; j < KEYS && kblk0 + j < sq.n; j += kWave * KW * IG) {
+    float t = sums[0][j];
+#pragma unroll
+    for (int x = 1; x < IG; ++x) t += sums[x][j];
+    a.score[sq.row0 + kblk0 + j] += t;
+  }
+}
+
+template <int D, int G, int NS, int KW, int IG>
+lethe_status launch_score(const PrefillArgs& a, long long blocks, hipStream_t s) {
+  if (blocks > 0x7fffffffLL) return LETHE_ERR_UNSUPPORTED;
+  hipLaunchKernelGGL((prefill_score_kernel<D, G, NS, KW, IG>), dim3((unsigned)blocks), dim3(kWave * KW * IG), 0, s, a);
+  return hipGetLastError() == hipSuccess ? LETHE_OK : LETHE_ERR_HIP;
 }
 
 template <int D, int G>
 lethe_status launch_prefill_dg(const PrefillArgs& a, hipStream_t s) {
   const long long segs = (long long)a.B * a.HK;
   const long long nq = (a.max_q + 31) / 32;
-  const long long fwd_blocks = segs * nq * ((G + 3) / 4);
-  const long long score_blocks = segs * ((a.max_kv + kPfKeysPerBlock - 1) / kPfKeysPerBlock);
-  if (fwd_blocks > 0x7fffffffLL || score_blocks > 0x7fffffffLL) return LETHE_ERR_UNSUPPORTED;
+  const long long fwd_blocks = segs * ((nq * G + kPfWaves - 1) / kPfWaves);
+  const long long wide = segs * ((a.max_kv + 127) / 128);
+  if (fwd_blocks > 0x7fffffffLL || wide > 0x7fffffffLL) return LETHE_ERR_UNSUPPORTED;
   if (fwd_blocks > 0) {
     hipLaunchKernelGGL((prefill_fwd_kernel<D, G>), dim3((unsigned)fwd_blocks), dim3(kPfThreads), 0, s, a);
     if (hipGetLastError() != hipSuccess) return LETHE_ERR_HIP;
   }
-  if (score_blocks > 0 && fwd_blocks > 0) {
-    hipLaunchKernelGGL((prefill_score_kernel<D, G>), dim3((unsigned)score_blocks), dim3(kPfThreads), 0, s, a);
-    if (hipGetLastError() != hipSuccess) return LETHE_ERR_HIP;
-  }
-  return LETHE_OK;
+  if (wide == 0 || fwd_blocks == 0) return LETHE_OK;
+  // 128 keys a block where those blocks fill the chip's 256 CUs, else 64 keys
+  // and eight item groups (24 segments of 77 to 421 rows: 12 us against 64 us
+  // with 256 keys a block).  At batch 8 and 2048 rows 128 keys in 8 waves take
+  // 2% less than 256 keys, 4% less than 64.
+  if (wide >= 256) return launch_score<D, G, 1, 4, 2>(a, wide, s);
+  return launch_score<D, G, 1, 2, 8>(a, segs * ((a.max_kv + 63) / 64), s);
 }
 
 template <int D>

@@ -437,6 +437,7 @@ lethe_status lethe_prefill_attn_score(const lethe_cache* c, int32_t layer, const
   a.q_rows = q_rows;
   a.max_q = max_q_len;
   a.max_kv = max_kv_len;
+  a.by_length = 0;  // chosen by the launcher
   a.scale_log2 = scale * 1.4426950408889634f;
   a.out = out;
   a.stat = (float*)ws;

@@ -247,6 +247,7 @@ struct PrefillArgs {
   const int32_t* q_len;   // [B]
   int64_t q_rows;
   int32_t max_q, max_kv;
+  int32_t by_length;      // forward blocks ordered over all sequences (set by the launcher)
   float scale_log2;       // softmax scale * log2(e)
   float* out;             // fp32 [q_rows][H_Q][D]
   float* stat;            // fp32 [q_rows][H_Q][2]: max (base 2), 1 / sum

@@ -33,6 +33,7 @@ namespace {
 constexpr int kPfThreads = 256;
 constexpr int kPfWaves = kPfThreads / kWave;
 constexpr float kPfNegBig = -1.0e30f;
+constexpr long long kPfResident = 512;  // forward blocks the chip holds at once
 
 typedef __bf16 pf_bf16x8_t __attribute__((ext_vector_type(8)));
 typedef __bf16 pf_bf16x4_t __attribute__((ext_vector_type(4)));
@@ -119,6 +120,65 @@ __device__ inline bool pf_seq(const PrefillArgs& a, int b, int h, PfSeq& sq) {
 // ---------------------------------------------------------------------------
 // Pass 1: outputs and per-query softmax statistics.
 // ---------------------------------------------------------------------------
+// The (sequence, KV head, four units) of a block.  Blocks start in the order
+// of their indices, so those with the most keys come first: last units first,
+// and, when the sequences differ and one lane can hold each (by_length), by
+// the 32-key bucket of a block's last key over all sequences.  A block runs
+// for up to half a millisecond and the grid is only a few times the 512
+// resident blocks, so a long sequence's blocks must not start last (four
+// chunks of about 1000 queries over 3001 to 12000 keys: 1012 us a call in unit
+// order, 811 us in this one; finding the block takes ten rounds of a wave sum).
+template <int G>
+__device__ inline bool pf_block(const PrefillArgs& a, int& b, int& h, int& ub) {
+  const int nub = ((a.max_q + 31) / 32 * G + kPfWaves - 1) / kPfWaves;
+  const int idx = (int)blockIdx.x;
+  if (a.by_length) {
+    const int lane = threadIdx.x & (kWave - 1);
+    const int bb = min(lane, a.B - 1);  // clamped: lanes past the last sequence repeat it
+    const int n = a.len[(long long)a.layer * a.B + bb];
+    const int qlen = a.q_len[bb];
+    if (!__all(n == __builtin_amdgcn_readfirstlane(n) && qlen == __builtin_amdgcn_readfirstlane(qlen))) {
+      // A sequence without queries or with sizes the checks refuse counts as
+      // one block, which runs those checks.
+      const bool work = n >= 0 && qlen > 0 && qlen <= n && qlen <= a.max_q && n <= a.max_kv;
+      const int nb = lane >= a.B ? 0 : work ? ((qlen + 31) / 32 * G + kPfWaves - 1) / kPfWaves : 1;
+      // Blocks of this lane's sequence (one head) whose last key is in bucket
+      // x or later: those from the unit of the first such tile on.
+      auto reach = [&](int x) {
+        if (x == 0) return nb;
+        if (!work || lane >= a.B || (n - 1) / 32 < x) return 0;
+        const int t = max(0, 32 * x - (n - qlen)) / 32;
+        return nb - max(0, t * G) / kPfWaves;
+      };
+      auto total = [&](int v) { return __builtin_amdgcn_readlane(wave_incl_scan_i32(v), kWave - 1) * a.HK; };
+      if (idx >= total(nb)) return false;
+      int lo = 0, hi = (a.max_kv + 31) / 32;  // buckets >= lo hold block idx, buckets >= hi do not
+      while (hi - lo > 1) {
+        const int mid = (lo + hi) / 2;
+        if (total(reach(mid)) > idx)
+          lo = mid;
+        else
+          hi = mid;
+      }
+      const int above = reach(lo + 1);
+      const int here = (reach(lo) - above) * a.HK;
+      const int r = idx - total(above);
+      const int incl = wave_incl_scan_i32(here);
+      b = (int)__builtin_ctzll(__ballot(incl > r));
+      const int o = r - __builtin_amdgcn_readlane(incl - here, b);
+      h = o % a.HK;
+      ub = __builtin_amdgcn_readlane(nb - 1 - above, b) - o / a.HK;
+      return true;
+    }
+  }
+  const int segs = a.B * a.HK;
+  const int seg = idx % segs;
+  ub = nub - 1 - idx / segs;
+  b = seg / a.HK;
+  h = seg % a.HK;
+  return true;
+}
+
 // Bound by the matrix cores at the clock the power limit leaves them: at
 // batch 8, 2048 tokens, Llama-8B heads, both passes do 550 GFLOP (P V in two
 // halves, S^T again in pass 2) in 0.61 ms, 0.90 PFLOP/s, where an 8192^3 bf16
@@ -146,11 +206,8 @@ __global__ __launch_bounds__(kPfThreads) __attribute__((amdgpu_waves_per_eu(2)))
   const int w = __builtin_amdgcn_readfirstlane(tid / kWave);
   const int hh = lane >> 5;  // lane half
   const int s = lane & 31;   // query column
-  const int segs = a.B * a.HK;
-  const int nub = ((a.max_q + 31) / 32 * G + kPfWaves - 1) / kPfWaves;
-  const int seg = blockIdx.x % segs;
-  const int ub = nub - 1 - (int)(blockIdx.x / segs);  // longest rows first
-  const int b = seg / a.HK, h = seg % a.HK;
+  int b, h, ub;
+  if (!pf_block<G>(a, b, h, ub)) return;
   PfSeq sq;
   if (!pf_seq(a, b, h, sq)) {
     if (tid == 0 && ub == 0) atomicOr(a.dev_status, LETHE_DEV_BAD_LAYOUT);
@@ -606,12 +663,14 @@ lethe_status launch_score(const PrefillArgs& a, long long blocks, hipStream_t s)
 }
 
 template <int D, int G>
-lethe_status launch_prefill_dg(const PrefillArgs& a, hipStream_t s) {
+lethe_status launch_prefill_dg(const PrefillArgs& args, hipStream_t s) {
+  PrefillArgs a = args;
   const long long segs = (long long)a.B * a.HK;
   const long long nq = (a.max_q + 31) / 32;
   const long long fwd_blocks = segs * ((nq * G + kPfWaves - 1) / kPfWaves);
   const long long wide = segs * ((a.max_kv + 127) / 128);
   if (fwd_blocks > 0x7fffffffLL || wide > 0x7fffffffLL) return LETHE_ERR_UNSUPPORTED;
+  a.by_length = a.B > 1 && a.B <= kWave && fwd_blocks > kPfResident;
   if (fwd_blocks > 0) {
     hipLaunchKernelGGL((prefill_fwd_kernel<D, G>), dim3((unsigned)fwd_blocks), dim3(kPfThreads), 0, s, a);
     if (hipGetLastError() != hipSuccess) return LETHE_ERR_HIP;

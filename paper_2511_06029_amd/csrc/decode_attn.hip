@@ -209,7 +209,8 @@ __device__ void finish_single(const DecodeArgs& a, const Chunk& ck, const Combin
 }
 
 // Last block of a segment: out and (M, 1/L) per head from the nne partials,
-// merged in batches of up to 16 chunks with online rescaling.
+// merged in batches of up to 16 chunks with online rescaling (a batch costs
+// one memory round trip, about 1.3 us).
 template <int D, int G>
 __device__ void combine_segment(const DecodeArgs& a, const Chunk& ck, const float* part, int nne) {
   constexpr int NB = 16;
@@ -674,14 +675,20 @@ __device__ void attn_chunk_mfma(const DecodeArgs& a, const Chunk& ck, const Read
 // ---------------------------------------------------------------------------
 // fp32 path (VALU): 16-byte loads, D/4 lanes per row.
 // ---------------------------------------------------------------------------
+template <int D>
+struct F32Cfg {
+  static constexpr int EPL = 4;             // elements per lane and row
+  static constexpr int LPR = D / EPL;       // lanes per row
+  static constexpr int RPW = kWave / LPR;   // rows a wavefront loads together
+  static constexpr int U = 4;               // such loads per step
+  static constexpr int STEP = U * RPW;      // rows per wavefront step
+};
+
 template <int D, int G, class ReadPending>
 __device__ void attn_chunk_f32(const DecodeArgs& a, const Chunk& ck, const ReadPending& read_pending,
                                CombineLds& cb) {
-  constexpr int EPL = 4;
-  constexpr int LPR = D / EPL;
-  constexpr int RPW = kWave / LPR;
-  constexpr int U = 4;
-  constexpr int ROWS_WAVE = U * RPW;
+  using Cfg = F32Cfg<D>;
+  constexpr int EPL = Cfg::EPL, LPR = Cfg::LPR, RPW = Cfg::RPW, U = Cfg::U, ROWS_WAVE = Cfg::STEP;
   const int tid = threadIdx.x;
   const int lane = tid & (kWave - 1);
   const int w = tid / kWave;
@@ -793,9 +800,8 @@ __device__ void attn_chunk_f32(const DecodeArgs& a, const Chunk& ck, const ReadP
   };
 
   int fixed_next = ck.first + w + ck.stride;
-  auto grab = [&]() { return step_index(step_request(ck, fixed_next, lane)); };
   int idx = ck.first + w;
-  for (; idx < nsteps; idx = grab()) {
+  while (idx < nsteps) {
     const int base = idx * ROWS_WAVE;
     uint4 kr[U], vr[U];
     int row[U];
@@ -811,7 +817,9 @@ __device__ void attn_chunk_f32(const DecodeArgs& a, const Chunk& ck, const ReadP
       vr[u] = *reinterpret_cast<const uint4*>(Vb + (long long)rr * D);
       sold[u] = (pstep && dp == 0 && row[u] < pre_end) ? pd.score[row[u]] : 0.0f;
     }
+    const int next = step_request(ck, fixed_next, lane);  // its reply comes during the step
     consume(kr, vr, valid, pstep, row, sold);
+    idx = step_index(next);
   }
   if (ck.app && idx == nsteps) {
     const long long nb = ((long long)ck.b * a.HK + ck.h) * D + dp * EPL;
@@ -913,6 +921,9 @@ struct BlockPlan {
   bool valid = false;             // the block has a chunk
 };
 
+// Decode blocks the chip holds at once: three on each of 256 CUs.
+constexpr int kResidentBlocks = 768;
+
 // Hinted steps are capped so that their sum over 1024 sequences stays an int.
 constexpr int kMaxHintSteps = 1 << 20;
 
@@ -949,22 +960,59 @@ __device__ inline BlockPlan plan_block(const DecodeArgs& a, int blk, SeqWords& w
     stp[r] = (in && hv[r] > 0) ? min((hv[r] + 31) >> 5, kMaxHintSteps) : 0;
     sum += stp[r];
   }
-  const long long total = (long long)__builtin_amdgcn_readlane(wave_incl_scan_i32(sum), kWave - 1) * a.HK;
-  int spb = 0;  // steps per chunk; 0: flat split
-  if (total > 0) {
+  // The arithmetic is in floats and kept short: every block runs it before its
+  // first load, and its instructions are fetched anew by every launch (integer
+  // divisions, two of them 64 bits wide, cost 0.3 us a call).
+  const int seq_steps = __builtin_amdgcn_readlane(wave_incl_scan_i32(sum), kWave - 1);
+  const float total = (float)seq_steps * (float)a.HK;
+  int spb = 0;         // steps per chunk; 0: flat split
+  float per_spb = 0.0f;
+  // Chunks of a sequence's segments: ceil(steps / spb), exact below 2^20 steps.
+  auto chunks = [&](int steps) {
+    return min(max((int)(((float)(steps + spb) - 0.5f) * per_spb), 1), kMaxChunksPerSeg);
+  };
+  auto set_spb = [&](int v) {
+    spb = v;
+    per_spb = __builtin_amdgcn_rcpf((float)v);
+  };
+  if (seq_steps > 0) {
     // Chunks of about steps_per_chunk hinted steps, between
     // min(min_chunks, nbt) and nbt chunks in all (nbt when the target is
-    // fixed).
-    long long nb = a.nbt;
-    if (a.adaptive) nb = min(max(total / a.steps_per_chunk, (long long)min(a.min_chunks, a.nbt)), (long long)a.nbt);
-    spb = (int)min((total + nb - 1) / nb, (long long)kMaxHintSteps);
+    // fixed).  (A quotient that rounds down passes nb by less than a chunk.)
+    int nb = a.nbt;
+    if (a.adaptive)
+      nb = (int)fminf(fmaxf(total * __builtin_amdgcn_rcpf((float)a.steps_per_chunk), (float)min(a.min_chunks, a.nbt)),
+                      (float)a.nbt);
+    int v = (int)fminf(ceilf(total * __builtin_amdgcn_rcpf((float)nb) * 0.999999f), (float)kMaxHintSteps);
+    // A chunk of fewer steps than wavefronts adds a partial and no loads (one
+    // sequence of 1111 rows: 35 chunks a segment, combined in three batches,
+    // 11.2 us a call; 9 chunks, 8.8 us).
+    if (a.adaptive) v = max(v, a.least_steps);
+    set_spb(max(v, 1));
+    // Rounding up to whole chunks can pass nb.  Where all nb blocks are
+    // resident at once the few more would share CUs that already hold their
+    // two, and those blocks, and the segments they belong to, end last (520
+    // and 528 blocks: 21 and 38 us where the others were done after 17 and
+    // 30).  Longer chunks until the blocks fit; with at most half as many
+    // segments as blocks that is at most twice the length.  Llama-8B batch 8,
+    // 2300-3100 rows: 26.5 -> 24.0 us a call; Qwen-7B batch 16, 4915-5200
+    // rows: 45.1 -> 38.6 us.
+    if (nb <= kResidentBlocks && 2LL * B * a.HK <= nb) {
+      for (;;) {
+        int cnt = 0;
+#pragma unroll
+        for (int r = 0; r < R; ++r) cnt += kWave * r + lane < B ? chunks(stp[r]) : 0;
+        if (__builtin_amdgcn_readlane(wave_incl_scan_i32(cnt), kWave - 1) * a.HK <= nb) break;
+        set_spb(spb + 1 + (spb >> 4));
+      }
+    }
   }
   BlockPlan p;
   int carry = 0;
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     const bool in = kWave * r + lane < B;
-    const int nch = spb > 0 ? min(max((stp[r] + spb - 1) / spb, 1), kMaxChunksPerSeg) : a.nch_flat;
+    const int nch = spb > 0 ? chunks(stp[r]) : a.nch_flat;
     const int cnt = in ? a.HK * nch : 0;
     const int incl = wave_incl_scan_i32(cnt);
     const int ex = carry + incl - cnt;
@@ -1079,7 +1127,13 @@ __device__ inline void decode_body(const DecodeArgs& a) {
   ck.c = c;
   ck.next = &a.seg_cnt[(long long)seg * kCntStride + kStepCounter];
   ck.first = c * kNumWaves;  // wave w starts at step c * waves + w
-  ck.stride = (a.deterministic && !kCompact) ? nch * kNumWaves : 0;
+  // Fixed steps too where the first round covers them all and leaves a wave
+  // for the appended row: nothing is left to balance, and no wave waits for a
+  // counter's reply (the one whose index equals the step count appends at
+  // once, its loads in flight with the steps').
+  constexpr int kStepRows = sizeof(T) == 2 ? MfmaCfg<D>::STEP : F32Cfg<D>::STEP;
+  const bool one_round = n <= (nch * kNumWaves - (app ? 1 : 0)) * kStepRows;
+  ck.stride = ((a.deterministic || one_round) && !kCompact) ? nch * kNumWaves : 0;
   // A compacting call fixes first steps only below t0 (rows that stay); the
   // counter hands out every step from there on.
   ck.dyn_base = kCompact ? min(nch * kNumWaves, t0) : nch * kNumWaves;
@@ -1494,6 +1548,8 @@ lethe_status launch_tdg(const DecodeArgs& a_in, hipStream_t s) {
   const int env_minc = env_int("LETHE_DECODE_MIN_CHUNKS");
   a.steps_per_chunk = env_spc > 0 ? env_spc : kStepsPerChunk;
   a.min_chunks = env_minc > 0 ? env_minc : kMinChunks;
+  // (fp32 steps are shorter, and its shorter sums keep the split they had.)
+  a.least_steps = sizeof(T) == 2 ? kNumWaves : 1;
   const int64_t segs = (int64_t)a.B * a.HK;
   // Flat split (no hints yet): at least four chunks per segment, so that with
   // many segments of ragged lengths the dispatcher hands the slots of early

@@ -60,19 +60,25 @@ struct Scores {
       return acc;
     }
   }
-  // The same for rows j[0 .. U) (valid indices): each head's loads of the U
-  // rows are issued together, unconditionally.
+  // The same for rows j[0 .. U) (valid indices): the loads of the U rows and
+  // of up to four heads are issued together, unconditionally (a head at a
+  // time they cost one memory latency each).
   template <int U>
   __device__ inline void batch(const int* j, float* v) const {
 #pragma unroll
     for (int u = 0; u < U; ++u) v[u] = s[j[u]];
     if constexpr (kShared) {
-      for (int h = 1; h < heads; ++h) {
-        float x[U];
+      for (int h0 = 1; h0 < heads; h0 += 4) {
+        float x[4][U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) x[u] = s[h * hstride + j[u]];
+        for (int hh = 0; hh < 4; ++hh)
 #pragma unroll
-        for (int u = 0; u < U; ++u) v[u] = v[u] + x[u];
+          for (int u = 0; u < U; ++u) x[hh][u] = s[min(h0 + hh, heads - 1) * hstride + j[u]];
+#pragma unroll
+        for (int hh = 0; hh < 4; ++hh)
+#pragma unroll
+          for (int u = 0; u < U; ++u)
+            if (h0 + hh < heads) v[u] = v[u] + x[hh][u];
       }
     }
   }
@@ -80,9 +86,8 @@ struct Scores {
 
 template <int NT>
 struct SelectShared {
-  uint32_t hist[256];
-  uint32_t suffix[257];
-  uint32_t digit, need;
+  uint32_t hist[2][256];
+  uint32_t digit, need, count;
   uint32_t red_u[NT / kWave];
   uint32_t red_c[NT / kWave];
   long long scan_tmp[NT / kWave + 1];
@@ -93,58 +98,55 @@ struct SelectShared {
 // by load latency).
 constexpr int kU = 8;
 
-// Key T of the m-th best key among rows [lo, hi) (m >= 1), how many rows
-// with key T belong to the best m, and how many rows have key T.  All
-// threads get the three.
-template <int NT, class KeyFn>
-__device__ void radix_select(const KeyFn& rank, int lo, int hi, uint32_t m, SelectShared<NT>& sh,
-                             uint32_t* T_out, uint32_t* need_out, uint32_t* count_out) {
+// MSB-first radix select over candidates that `count_digits(hist, shift,
+// prefix, pmask)` counts by the 8-bit digit at `shift` (those whose bits under
+// pmask equal prefix): key T of the m-th best (m >= 1), how many candidates
+// with key T belong to the best m, and how many have it; all threads get the
+// three.  A digit whose candidates are all needed ends the search: T is then
+// the lowest key of that digit, and the two counts are equal.  With keys that
+// spread (accumulated attention) two or three of the four passes run.
+// Bound by latency: two barriers a pass, the next histogram cleared while the
+// first wave searches this one (five barriers and four passes: 91 us against
+// 71 us for the 32768 segments of the batch-128 round).
+template <int NT, class CountFn>
+__device__ void radix_select(const CountFn& count_digits, uint32_t m, SelectShared<NT>& sh, uint32_t* T_out,
+                             uint32_t* need_out, uint32_t* count_out) {
   const int tid = threadIdx.x;
   uint32_t prefix = 0, pmask = 0, need = m, count = 0;
-  for (int shift = 24; shift >= 0; shift -= 8) {
-    if (tid < 256) sh.hist[tid] = 0;
+  if (tid < 256) sh.hist[0][tid] = 0;
+  __syncthreads();
+  int cur = 0;
+  for (int shift = 24; shift >= 0; shift -= 8, cur ^= 1) {
+    count_digits(sh.hist[cur], shift, prefix, pmask);
     __syncthreads();
-    for (int j0 = lo; j0 < hi; j0 += kU * NT) {
-      int jj[kU];
-      float v[kU];
-#pragma unroll
-      for (int u = 0; u < kU; ++u) jj[u] = min(j0 + u * NT + tid, hi - 1);
-      rank.template batch<kU>(jj, v);
-#pragma unroll
-      for (int u = 0; u < kU; ++u) {
-        const uint32_t key = order_key(v[u]);
-        if (j0 + u * NT + tid < hi && (key & pmask) == prefix) atomicAdd(&sh.hist[(key >> shift) & 255u], 1u);
-      }
-    }
-    __syncthreads();
-    // suffix[d] = matching keys whose digit is >= d: wave 0, four bins a lane.
     if (tid < kWave) {
-      const uint32_t h0 = sh.hist[4 * tid], h1 = sh.hist[4 * tid + 1];
-      const uint32_t h2 = sh.hist[4 * tid + 2], h3 = sh.hist[4 * tid + 3];
+      // suffix[d] = matching keys whose digit is >= d: four bins a lane; the
+      // digit is the largest one whose suffix reaches need.
+      const uint32_t h0 = sh.hist[cur][4 * tid], h1 = sh.hist[cur][4 * tid + 1];
+      const uint32_t h2 = sh.hist[cur][4 * tid + 2], h3 = sh.hist[cur][4 * tid + 3];
       const uint32_t tot = h0 + h1 + h2 + h3;
       uint32_t incl = tot;  // sum over lanes tid .. 63
       for (int o = 1; o < kWave; o <<= 1) {
         const uint32_t v = __shfl_down(incl, o);
         if (tid + o < kWave) incl += v;
       }
-      const uint32_t above = incl - tot;
-      sh.suffix[4 * tid + 3] = above + h3;
-      sh.suffix[4 * tid + 2] = above + h3 + h2;
-      sh.suffix[4 * tid + 1] = above + h3 + h2 + h1;
-      sh.suffix[4 * tid] = incl;
-      if (tid == 0) sh.suffix[256] = 0;
+      const uint32_t s4 = incl - tot, s3 = s4 + h3, s2 = s3 + h2, s1 = s2 + h1;
+      if (incl >= need && s4 < need) {
+        const int d = s3 >= need ? 3 : s2 >= need ? 2 : s1 >= need ? 1 : 0;
+        sh.digit = (uint32_t)(4 * tid + d);
+        sh.need = need - (d == 3 ? s4 : d == 2 ? s3 : d == 1 ? s2 : s1);
+        sh.count = d == 3 ? h3 : d == 2 ? h2 : d == 1 ? h1 : h0;
+      }
     }
-    __syncthreads();
-    if (tid < 256 && sh.suffix[tid] >= need && sh.suffix[tid + 1] < need) {
-      sh.digit = (uint32_t)tid;
-      sh.need = need - sh.suffix[tid + 1];
-    }
+    // The other histogram, for the next pass (by the last threads: the first
+    // wave is busy).
+    if (tid >= NT - 256) sh.hist[cur ^ 1][tid - (NT - 256)] = 0;
     __syncthreads();
     prefix |= sh.digit << shift;
     pmask |= 255u << shift;
     need = sh.need;
-    count = sh.hist[sh.digit];
-    __syncthreads();
+    count = sh.count;
+    if (need == count) break;
   }
   *T_out = prefix;
   *need_out = need;
@@ -154,54 +156,6 @@ __device__ void radix_select(const KeyFn& rank, int lo, int hi, uint32_t m, Sele
 // Keys a thread keeps in registers: candidate sets of up to kRegKeys * NT rows
 // are read from memory once.
 constexpr int kRegKeys = 32;
-
-// radix_select over keys held in registers: thread t holds the keys of
-// candidates t, t + NT, ... (key[u] for u < cnt; cnt is the same for all
-// threads, slots past the candidates hold 0 and are not counted).
-template <int NT>
-__device__ void radix_select_regs(const uint32_t (&key)[kRegKeys], const bool (&valid)[kRegKeys], uint32_t m,
-                                  SelectShared<NT>& sh, uint32_t* T_out, uint32_t* need_out, uint32_t* count_out) {
-  const int tid = threadIdx.x;
-  uint32_t prefix = 0, pmask = 0, need = m, count = 0;
-  for (int shift = 24; shift >= 0; shift -= 8) {
-    if (tid < 256) sh.hist[tid] = 0;
-    __syncthreads();
-#pragma unroll
-    for (int u = 0; u < kRegKeys; ++u)
-      if (valid[u] && (key[u] & pmask) == prefix) atomicAdd(&sh.hist[(key[u] >> shift) & 255u], 1u);
-    __syncthreads();
-    if (tid < kWave) {
-      const uint32_t h0 = sh.hist[4 * tid], h1 = sh.hist[4 * tid + 1];
-      const uint32_t h2 = sh.hist[4 * tid + 2], h3 = sh.hist[4 * tid + 3];
-      const uint32_t tot = h0 + h1 + h2 + h3;
-      uint32_t incl = tot;
-      for (int o = 1; o < kWave; o <<= 1) {
-        const uint32_t v = __shfl_down(incl, o);
-        if (tid + o < kWave) incl += v;
-      }
-      const uint32_t above = incl - tot;
-      sh.suffix[4 * tid + 3] = above + h3;
-      sh.suffix[4 * tid + 2] = above + h3 + h2;
-      sh.suffix[4 * tid + 1] = above + h3 + h2 + h1;
-      sh.suffix[4 * tid] = incl;
-      if (tid == 0) sh.suffix[256] = 0;
-    }
-    __syncthreads();
-    if (tid < 256 && sh.suffix[tid] >= need && sh.suffix[tid + 1] < need) {
-      sh.digit = (uint32_t)tid;
-      sh.need = need - sh.suffix[tid + 1];
-    }
-    __syncthreads();
-    prefix |= sh.digit << shift;
-    pmask |= 255u << shift;
-    need = sh.need;
-    count = sh.hist[sh.digit];
-    __syncthreads();
-  }
-  *T_out = prefix;
-  *need_out = need;
-  *count_out = count;
-}
 
 // Block-wide max of a key and sum of a count; every thread gets both.
 template <int NT>
@@ -249,6 +203,34 @@ __global__ __launch_bounds__(NT) void select_kernel(SelectArgs a) {
   const int nheads = kShared ? a.HK : 1;
   __shared__ SelectShared<NT> sh;
 
+  // The keys of rows [from, to) in registers, read once (eight rows' loads at
+  // a time): row from + u NT + tid is slot u.
+  uint32_t key[kRegKeys];
+  bool valid[kRegKeys];
+  auto load_keys = [&](int from, int to) {
+#pragma unroll
+    for (int u0 = 0; u0 < kRegKeys; u0 += kU) {
+      if (from + u0 * NT < to) {  // block-uniform
+        int jj[kU];
+        float v[kU];
+#pragma unroll
+        for (int u = 0; u < kU; ++u) jj[u] = min(from + (u0 + u) * NT + tid, to - 1);
+        rank.template batch<kU>(jj, v);
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+          valid[u0 + u] = from + (u0 + u) * NT + tid < to;
+          key[u0 + u] = valid[u0 + u] ? order_key(v[u]) : 0u;
+        }
+      } else {
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+          valid[u0 + u] = false;
+          key[u0 + u] = 0u;
+        }
+      }
+    }
+  };
+
   // Plan: candidate rows [lo, hi), how many of them to keep (m), and the
   // forced rows, which are [0, fs) and [fr, n).
   int lo = 0, hi = 0, m = 0, fs = 0, fr = n;
@@ -274,14 +256,25 @@ __global__ __launch_bounds__(NT) void select_kernel(SelectArgs a) {
     if (n <= lev0) {
       all = true;
     } else {
-      // Head of the ranking and the NaN count.
+      // Head of the ranking and the NaN count (whose key is 0, and only
+      // theirs), from registers where they hold every row.
+      const bool regs = n <= kRegKeys * NT;
       uint32_t kmax = 0, nnan = 0;
       {
         uint32_t km = 0, cn = 0;
-        for (int j = tid; j < n; j += NT) {
-          const float v = rank(j);
-          km = max(km, order_key(v));
-          cn += (v != v) ? 1u : 0u;
+        if (regs) {
+          load_keys(0, n);
+#pragma unroll
+          for (int u = 0; u < kRegKeys; ++u) {
+            km = max(km, key[u]);  // slots past the rows hold 0
+            cn += valid[u] && key[u] == 0u ? 1u : 0u;
+          }
+        } else {
+          for (int j = tid; j < n; j += NT) {
+            const float v = rank(j);
+            km = max(km, order_key(v));
+            cn += (v != v) ? 1u : 0u;
+          }
         }
         block_max_count<NT>(km, cn, sh, &kmax, &nnan);
       }
@@ -292,9 +285,15 @@ __global__ __launch_bounds__(NT) void select_kernel(SelectArgs a) {
         // head, exact in fp64): ranks [cnt, n - nnan) pass the test.
         const double dh = (double)head, dt = (double)a.tau;
         uint32_t cn = 0, unused = 0;
-        for (int j = tid; j < n; j += NT) {
-          const float v = rank(j);
-          cn += (v == v && dt * (double)v > dh) ? 1u : 0u;
+        if (regs) {
+#pragma unroll
+          for (int u = 0; u < kRegKeys; ++u)
+            cn += (valid[u] && key[u] != 0u && dt * (double)key_value(key[u]) > dh) ? 1u : 0u;
+        } else {
+          for (int j = tid; j < n; j += NT) {
+            const float v = rank(j);
+            cn += (v == v && dt * (double)v > dh) ? 1u : 0u;
+          }
         }
         uint32_t cnt = 0;
         block_max_count<NT>(0u, cn, sh, &unused, &cnt);
@@ -332,32 +331,13 @@ __global__ __launch_bounds__(NT) void select_kernel(SelectArgs a) {
   }
   uint32_t T = 0, need = 0, countT = 0;
   if (m > 0 && hi - lo <= kRegKeys * NT) {
-    // The candidates' keys in registers, read once (eight rows' loads at a
-    // time); the radix passes and the keep pass use them.
-    uint32_t key[kRegKeys];
-    bool valid[kRegKeys];
+    if constexpr (!kShrink) load_keys(lo, hi);
+    auto count_digits = [&](uint32_t* hist, int shift, uint32_t prefix, uint32_t pmask) {
 #pragma unroll
-    for (int u0 = 0; u0 < kRegKeys; u0 += kU) {
-      if (lo + u0 * NT < hi) {  // block-uniform
-        int jj[kU];
-        float v[kU];
-#pragma unroll
-        for (int u = 0; u < kU; ++u) jj[u] = min(lo + (u0 + u) * NT + tid, hi - 1);
-        rank.template batch<kU>(jj, v);
-#pragma unroll
-        for (int u = 0; u < kU; ++u) {
-          valid[u0 + u] = lo + (u0 + u) * NT + tid < hi;
-          key[u0 + u] = order_key(v[u]);
-        }
-      } else {
-#pragma unroll
-        for (int u = 0; u < kU; ++u) {
-          valid[u0 + u] = false;
-          key[u0 + u] = 0u;
-        }
-      }
-    }
-    radix_select_regs<NT>(key, valid, (uint32_t)m, sh, &T, &need, &countT);
+      for (int u = 0; u < kRegKeys; ++u)
+        if (valid[u] && (key[u] & pmask) == prefix) atomicAdd(&hist[(key[u] >> shift) & 255u], 1u);
+    };
+    radix_select<NT>(count_digits, (uint32_t)m, sh, &T, &need, &countT);
     if (need == countT) {
       // Forced rows, then every candidate at or above T.
       for (int j = tid; j < fs; j += NT)
@@ -375,7 +355,21 @@ __global__ __launch_bounds__(NT) void select_kernel(SelectArgs a) {
       return;
     }
   } else if (m > 0) {
-    radix_select<NT>(rank, lo, hi, (uint32_t)m, sh, &T, &need, &countT);
+    auto count_digits = [&](uint32_t* hist, int shift, uint32_t prefix, uint32_t pmask) {
+      for (int j0 = lo; j0 < hi; j0 += kU * NT) {
+        int jj[kU];
+        float v[kU];
+#pragma unroll
+        for (int u = 0; u < kU; ++u) jj[u] = min(j0 + u * NT + tid, hi - 1);
+        rank.template batch<kU>(jj, v);
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+          const uint32_t k = order_key(v[u]);
+          if (j0 + u * NT + tid < hi && (k & pmask) == prefix) atomicAdd(&hist[(k >> shift) & 255u], 1u);
+        }
+      }
+    };
+    radix_select<NT>(count_digits, (uint32_t)m, sh, &T, &need, &countT);
   }
   if (m == 0 || need == countT) {
     // Every candidate with key T is kept (or none is a candidate to keep):

@@ -166,7 +166,8 @@ __global__ __launch_bounds__(kWave) void budget_kernel(SparsityArgs a) {
     unsigned long long taken = 0;
 #pragma unroll
     for (int k = 0; k < kLpl; ++k) {
-      q[k] = act[k] ? (R * w[k]) / W : 0ull;
+      q[k] = 0ull;
+      if (kWave * k < L) q[k] = act[k] ? (R * w[k]) / W : 0ull;  // no divisions for layers past the last
       const bool cap_k = act[k] && (unsigned long long)f[k] + q[k] >= (unsigned long long)cp[k];
       capped_any |= cap_k;
       if (cap_k) taken += (unsigned long long)(cp[k] - f[k]);
@@ -197,22 +198,21 @@ __global__ __launch_bounds__(kWave) void budget_kernel(SparsityArgs a) {
     int rank[kLpl];
 #pragma unroll
     for (int k = 0; k < kLpl; ++k) rank[k] = 0;
-    for (int j = 0; j < L; ++j) {
-      const int jl = j % kWave, jk = j / kWave;
-      unsigned long long rj = 0;
-      bool aj = false;
 #pragma unroll
-      for (int k = 0; k < kLpl; ++k) {
-        if (k == jk) {
-          rj = __shfl(rem[k], jl);
-          aj = __shfl(act[k] ? 1 : 0, jl) != 0;
+    for (int jk = 0; jk < kLpl; ++jk) {
+      // Each active layer's remainder through scalar registers (shuffles, over
+      // every layer, cost two memory-like latencies each).
+      for (unsigned long long on = __ballot(act[jk]); on != 0ull; on &= on - 1ull) {
+        const int jl = (int)__builtin_ctzll(on);
+        const unsigned long long rj =
+            ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(rem[jk] >> 32), jl) << 32) |
+            (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)rem[jk], jl);
+        const int j = jl + kWave * jk;
+#pragma unroll
+        for (int k = 0; k < kLpl; ++k) {
+          const int l = lane + kWave * k;
+          if (act[k] && (rj > rem[k] || (rj == rem[k] && j < l))) ++rank[k];
         }
-      }
-      if (!aj) continue;
-#pragma unroll
-      for (int k = 0; k < kLpl; ++k) {
-        const int l = lane + kWave * k;
-        if (act[k] && (rj > rem[k] || (rj == rem[k] && j < l))) ++rank[k];
       }
     }
 #pragma unroll

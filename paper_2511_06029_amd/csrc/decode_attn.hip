@@ -957,7 +957,7 @@ __device__ inline BlockPlan plan_block(const DecodeArgs& a, int blk, SeqWords& w
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     const bool in = kWave * r + lane < B;
-    stp[r] = (in && hv[r] > 0) ? min((hv[r] + 31) >> 5, kMaxHintSteps) : 0;
+    stp[r] = (in && hv[r] > 0) ? min(((hv[r] + 31) >> 5) + a.spare_steps, kMaxHintSteps) : 0;
     sum += stp[r];
   }
   // The arithmetic is in floats and kept short: every block runs it before its
@@ -997,7 +997,7 @@ __device__ inline BlockPlan plan_block(const DecodeArgs& a, int blk, SeqWords& w
     // segments as blocks that is at most twice the length.  Llama-8B batch 8,
     // 2300-3100 rows: 26.5 -> 24.0 us a call; Qwen-7B batch 16, 4915-5200
     // rows: 45.1 -> 38.6 us.
-    if (nb <= kResidentBlocks && 2LL * B * a.HK <= nb) {
+    if (a.fit && nb <= kResidentBlocks && 2LL * B * a.HK <= nb) {
       for (;;) {
         int cnt = 0;
 #pragma unroll
@@ -1548,8 +1548,14 @@ lethe_status launch_tdg(const DecodeArgs& a_in, hipStream_t s) {
   const int env_minc = env_int("LETHE_DECODE_MIN_CHUNKS");
   a.steps_per_chunk = env_spc > 0 ? env_spc : kStepsPerChunk;
   a.min_chunks = env_minc > 0 ? env_minc : kMinChunks;
-  // (fp32 steps are shorter, and its shorter sums keep the split they had.)
+  // One step more than the hint has, for the appended row and those a sequence
+  // gains until its next hint, so that a short segment's first round still
+  // covers it (two sequences of 619 to 688 rows, 2 KV heads: 11.4 us a call;
+  // 12.1 without, where 20 waves take a second round for the last rows).  fp32
+  // steps and sums are shorter and keep the split they had.
   a.least_steps = sizeof(T) == 2 ? kNumWaves : 1;
+  a.spare_steps = sizeof(T) == 2 && a.adaptive ? 1 : 0;
+  a.fit = sizeof(T) == 2;
   const int64_t segs = (int64_t)a.B * a.HK;
   // Flat split (no hints yet): at least four chunks per segment, so that with
   // many segments of ragged lengths the dispatcher hands the slots of early

@@ -21,7 +21,7 @@
 //     there are no atomics and the result does not depend on scheduling.
 #include <math.h>
 
-#include <type_traits>
+#include <algorithm>
 
 #include "device_common.h"
 #include "lethe_internal.h"
@@ -130,7 +130,7 @@ __device__ inline bool pf_seq(const PrefillArgs& a, int b, int h, PfSeq& sq) {
 // order, 811 us in this one; finding the block takes ten rounds of a wave sum).
 template <int G>
 __device__ inline bool pf_block(const PrefillArgs& a, int& b, int& h, int& ub) {
-  const int nub = ((a.max_q + 31) / 32 * G + kPfWaves - 1) / kPfWaves;
+  const int segs = a.B * a.HK;
   const int idx = (int)blockIdx.x;
   if (a.by_length) {
     const int lane = threadIdx.x & (kWave - 1);
@@ -152,7 +152,7 @@ __device__ inline bool pf_block(const PrefillArgs& a, int& b, int& h, int& ub) {
       };
       auto total = [&](int v) { return __builtin_amdgcn_readlane(wave_incl_scan_i32(v), kWave - 1) * a.HK; };
       if (idx >= total(nb)) return false;
-      int lo = 0, hi = (a.max_kv + 31) / 32;  // buckets >= lo hold block idx, buckets >= hi do not
+      int lo = 0, hi = a.max_kv / 32 + 1;  // buckets >= lo hold block idx, buckets >= hi do not
       while (hi - lo > 1) {
         const int mid = (lo + hi) / 2;
         if (total(reach(mid)) > idx)
@@ -171,9 +171,8 @@ __device__ inline bool pf_block(const PrefillArgs& a, int& b, int& h, int& ub) {
       return true;
     }
   }
-  const int segs = a.B * a.HK;
   const int seg = idx % segs;
-  ub = nub - 1 - idx / segs;
+  ub = (int)gridDim.x / segs - 1 - idx / segs;
   b = seg / a.HK;
   h = seg % a.HK;
   return true;
@@ -523,14 +522,12 @@ __global__ __launch_bounds__(kWave * KW * IG) __attribute__((amdgpu_waves_per_eu
   const int kw = w % KW, ig = w / KW;
   const int hh = lane >> 5;
   const int s = lane & 31;
-  const int segs = a.B * a.HK;
-  const int seg = blockIdx.x % segs;
-  const int kb = blockIdx.x / segs;  // low keys (most queries) first
-  const int b = seg / a.HK, h = seg % a.HK;
+  const int b = (int)blockIdx.x / a.HK, h = (int)blockIdx.x % a.HK;
+  const long long kb = blockIdx.y + (long long)gridDim.y * blockIdx.z;  // low keys (most queries) first
   PfSeq sq;
   if (!pf_seq(a, b, h, sq)) return;  // flagged by the forward pass
-  const int kblk0 = KEYS * kb;
-  if (sq.qlen == 0 || kblk0 >= sq.n) return;
+  if (sq.qlen == 0 || kb * KEYS >= sq.n) return;
+  const int kblk0 = (int)kb * KEYS;
   const int HQ = a.HK * G;
   const int j0w = kblk0 + 32 * NS * kw;
   const char* Kb = reinterpret_cast<const char*>(a.k) + sq.row0 * ROWB;
@@ -655,33 +652,45 @@ __global__ __launch_bounds__(kWave * KW * IG) __attribute__((amdgpu_waves_per_eu
   }
 }
 
+// One block per segment (x) and key block (y, then z).  max_kv is only a bound:
+// a grid of one dimension would be refused from 2^32 threads on (1024 segments
+// and a bound of 2^20 rows), whatever the lengths are.
 template <int D, int G, int NS, int KW, int IG>
-lethe_status launch_score(const PrefillArgs& a, long long blocks, hipStream_t s) {
-  if (blocks > 0x7fffffffLL) return LETHE_ERR_UNSUPPORTED;
-  hipLaunchKernelGGL((prefill_score_kernel<D, G, NS, KW, IG>), dim3((unsigned)blocks), dim3(kWave * KW * IG), 0, s, a);
+lethe_status launch_score(const PrefillArgs& a, unsigned segs, hipStream_t s) {
+  constexpr long long kKeys = 32 * NS * KW, kMaxY = 32768;
+  const long long kblocks = (a.max_kv + kKeys - 1) / kKeys;
+  const unsigned y = (unsigned)std::min(kblocks, kMaxY), z = (unsigned)((kblocks + y - 1) / y);
+  hipLaunchKernelGGL((prefill_score_kernel<D, G, NS, KW, IG>), dim3(segs, y, z), dim3(kWave * KW * IG), 0, s, a);
   return hipGetLastError() == hipSuccess ? LETHE_OK : LETHE_ERR_HIP;
 }
 
 template <int D, int G>
 lethe_status launch_prefill_dg(const PrefillArgs& args, hipStream_t s) {
   PrefillArgs a = args;
+  // The bounds a caller passes may be loose (INT32_MAX): no sequence that
+  // passes the kernels' checks has more queries than there are query rows or
+  // more rows than a segment of this layer can have.
+  a.max_q = (int32_t)std::min<int64_t>(a.max_q, std::max<int64_t>(a.q_rows, 1));
+  a.max_kv = (int32_t)std::min<int64_t>(a.max_kv, a.rows_per_layer / a.HK);
   const long long segs = (long long)a.B * a.HK;
-  const long long nq = (a.max_q + 31) / 32;
+  const long long nq = (a.max_q + 31LL) / 32;
   const long long fwd_blocks = segs * ((nq * G + kPfWaves - 1) / kPfWaves);
-  const long long wide = segs * ((a.max_kv + 127) / 128);
-  if (fwd_blocks > 0x7fffffffLL || wide > 0x7fffffffLL) return LETHE_ERR_UNSUPPORTED;
+  // A launch's threads in x must stay below 2^32; refused before the first one
+  // (from 256 segments on the score blocks have 512 threads).
+  if (fwd_blocks * kPfThreads > 0xffffffffLL || segs * 512 > 0xffffffffLL) return LETHE_ERR_UNSUPPORTED;
   a.by_length = a.B > 1 && a.B <= kWave && fwd_blocks > kPfResident;
   if (fwd_blocks > 0) {
     hipLaunchKernelGGL((prefill_fwd_kernel<D, G>), dim3((unsigned)fwd_blocks), dim3(kPfThreads), 0, s, a);
     if (hipGetLastError() != hipSuccess) return LETHE_ERR_HIP;
   }
+  const long long wide = segs * ((a.max_kv + 127LL) / 128);
   if (wide == 0 || fwd_blocks == 0) return LETHE_OK;
   // 128 keys a block where those blocks fill the chip's 256 CUs, else 64 keys
   // and eight item groups (24 segments of 77 to 421 rows: 12 us against 64 us
   // with 256 keys a block).  At batch 8 and 2048 rows 128 keys in 8 waves take
   // 2% less than 256 keys, 4% less than 64.
-  if (wide >= 256) return launch_score<D, G, 1, 4, 2>(a, wide, s);
-  return launch_score<D, G, 1, 2, 8>(a, segs * ((a.max_kv + 63) / 64), s);
+  if (wide >= 256) return launch_score<D, G, 1, 4, 2>(a, (unsigned)segs, s);
+  return launch_score<D, G, 1, 2, 8>(a, (unsigned)segs, s);
 }
 
 template <int D>

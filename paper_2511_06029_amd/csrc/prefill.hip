@@ -22,6 +22,7 @@
 #include <math.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "device_common.h"
 #include "lethe_internal.h"
@@ -282,6 +283,7 @@ __global__ __launch_bounds__(kPfThreads) __attribute__((amdgpu_waves_per_eu(2)))
 
   const int pos = p0 + s;  // this lane's query position
   float m = kPfNegBig, l = 0.0f, corr = 1.0f;
+  float lost = 0.0f;  // last step: sum of the weights less their two halves
   pf_f32x16_t o[NT];
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt)
@@ -351,9 +353,15 @@ __global__ __launch_bounds__(kPfThreads) __attribute__((amdgpu_waves_per_eu(2)))
   };
   // P of 16 keys in bf16 high and low parts: registers 8 (mm % 2) .. of
   // sub-tile mm / 2 are the B operand of those keys in the order (j < 4:
-  // 4 hh + j, else 8 + 4 hh + j - 4) that the V^T operand follows.
+  // 4 hh + j, else 8 + 4 hh + j - 4) that the V^T operand follows.  A wave's
+  // last step also sums what the two halves miss (up to 2^-18 of a weight), and
+  // the output is divided by the sum of the weights it was made of: a row whose
+  // weight lies on a few keys then keeps their exact ratio.  Errors against 64
+  // bits, batch 8 x 2048 and three prompts of 77 to 421 rows: 1.686e-6 and
+  // 1.510e-6 without, 1.663e-6 and 1.465e-6 with it (0.2% of the time); every
+  // step counted, 1.652e-6 and 1.456e-6 (6%).
   float psum[2] = {0.0f, 0.0f};
-  auto weights = [&](const pf_f32x16_t (&x)[2], int mm, pf_bf16x8_t& ph, pf_bf16x8_t& pl) {
+  auto weights = [&](const pf_f32x16_t (&x)[2], int mm, pf_bf16x8_t& ph, pf_bf16x8_t& pl, auto last) {
 #pragma unroll
     for (int j = 0; j < 8; j += 2) {
       const float pa = hw_exp2(fmaf(x[mm >> 1][8 * (mm & 1) + j], sc, -m));
@@ -362,8 +370,12 @@ __global__ __launch_bounds__(kPfThreads) __attribute__((amdgpu_waves_per_eu(2)))
       psum[1] += pb;
       const pf_bf16x2_t hi = __builtin_convertvector((pf_f32x2_t{pa, pb}), pf_bf16x2_t);
       const unsigned hb = __builtin_bit_cast(unsigned, hi);
-      const pf_bf16x2_t lo = __builtin_convertvector(
-          (pf_f32x2_t{pa - __uint_as_float(hb << 16), pb - __uint_as_float(hb & 0xffff0000u)}), pf_bf16x2_t);
+      const float ra = pa - __uint_as_float(hb << 16), rb = pb - __uint_as_float(hb & 0xffff0000u);
+      const pf_bf16x2_t lo = __builtin_convertvector((pf_f32x2_t{ra, rb}), pf_bf16x2_t);
+      if constexpr (last) {
+        const unsigned lb = __builtin_bit_cast(unsigned, lo);
+        lost += (ra - __uint_as_float(lb << 16)) + (rb - __uint_as_float(lb & 0xffff0000u));
+      }
       ph[j] = hi[0];
       ph[j + 1] = hi[1];
       pl[j] = lo[0];
@@ -388,12 +400,12 @@ __global__ __launch_bounds__(kPfThreads) __attribute__((amdgpu_waves_per_eu(2)))
     clear(sn);
     psum[0] = psum[1] = 0.0f;
     pf_bf16x8_t ph, pl, nh, nl;
-    weights(sx, 0, ph, pl);
+    weights(sx, 0, ph, pl, std::false_type());
 #pragma unroll
     for (int kk = 0; kk < KS / 4; ++kk) qk(sn, knext, kk);
 #pragma unroll
     for (int mm = 1; mm < 4; ++mm) {
-      weights(sx, mm, nh, nl);
+      weights(sx, mm, nh, nl, std::false_type());
 #pragma unroll
       for (int kk = mm * KS / 4; kk < (mm + 1) * KS / 4; ++kk) qk(sn, knext, kk);
       pv(vcur, mm - 1, ph, pl);
@@ -414,7 +426,7 @@ __global__ __launch_bounds__(kPfThreads) __attribute__((amdgpu_waves_per_eu(2)))
 #pragma unroll
     for (int mm = 0; mm < 4; ++mm) {
       pf_bf16x8_t ph, pl;
-      weights(sx, mm, ph, pl);
+      weights(sx, mm, ph, pl, std::true_type());
       if constexpr (G % kPfWaves == 0) {
         pv(vcur, mm, ph, pl);
       } else {
@@ -477,18 +489,20 @@ __global__ __launch_bounds__(kPfThreads) __attribute__((amdgpu_waves_per_eu(2)))
   for (; st < nsteps; ++st) advance(st, (st & 1) ? ktile1 : ktile0, (st & 1) ? vtile0 : vtile1);
   if (!active) return;
 
-  // l is split over the two lane halves of a query column; m is common.
+  // l and lost are split over the two lane halves of a query column; m is
+  // common.  The statistics keep the exact sum.
   l += __shfl_xor(l, 32);
+  lost += __shfl_xor(lost, 32);
   const int i = 32 * pt + s;
   if (i >= sq.qlen) return;
-  const float inv = 1.0f / l;
+  const float inv = 1.0f / l, winv = 1.0f / (l - lost);
   float* orow = a.out + ((sq.q0 + i) * HQ + (long long)h * G + g) * D;
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
     for (int r = 0; r < 16; r += 4)
       *reinterpret_cast<float4*>(orow + 32 * nt + 2 * r + 4 * hh) =
-          make_float4(o[nt][r] * inv, o[nt][r + 1] * inv, o[nt][r + 2] * inv, o[nt][r + 3] * inv);
+          make_float4(o[nt][r] * winv, o[nt][r + 1] * winv, o[nt][r + 2] * winv, o[nt][r + 3] * winv);
   if (hh == 0)
     *reinterpret_cast<float2*>(a.stat + 2 * ((long long)(h * G + g) * a.q_rows + sq.q0 + i)) = make_float2(m, inv);
 }

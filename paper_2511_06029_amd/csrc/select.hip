@@ -205,28 +205,48 @@ __global__ __launch_bounds__(NT) void select_kernel(SelectArgs a) {
   __shared__ SelectShared<NT> sh;
 
   // The keys of rows [from, to) in registers, read once (eight rows' loads at
-  // a time): row from + u NT + tid is slot u.
+  // a time, two where the head sums of two rows a thread are all): row from +
+  // u NT + tid is slot u.  Every pass over them leaves out the groups of eight
+  // slots past the last row by a block-uniform branch, and no slot's liveness
+  // is kept: as 32 stored lane masks it spilled scalar registers (154 of
+  // them in Algorithm 1's kernel), and passes over 32 slots whatever the length
+  // took 64.2 us for Algorithm 1 on 1024 lists of 1000 rows and two heads and
+  // 40.2 us for the per-head masks of 8192 segments of 1000 rows (as it is, 38.8
+  // and 27.6 us).
   uint32_t key[kRegKeys];
-  bool valid[kRegKeys];
   auto load_keys = [&](int from, int to) {
+    if (kShared && to - from <= 2 * NT) {
+      int jj[2];
+      float v[2];
+#pragma unroll
+      for (int u = 0; u < 2; ++u) jj[u] = min(from + u * NT + tid, to - 1);
+      rank.template batch<2>(jj, v);
+#pragma unroll
+      for (int u = 0; u < 2; ++u) key[u] = order_key(v[u]);
+      return;
+    }
 #pragma unroll
     for (int u0 = 0; u0 < kRegKeys; u0 += kU) {
-      if (from + u0 * NT < to) {  // block-uniform
+      if (from + u0 * NT < to) {
         int jj[kU];
         float v[kU];
 #pragma unroll
         for (int u = 0; u < kU; ++u) jj[u] = min(from + (u0 + u) * NT + tid, to - 1);
         rank.template batch<kU>(jj, v);
 #pragma unroll
-        for (int u = 0; u < kU; ++u) {
-          valid[u0 + u] = from + (u0 + u) * NT + tid < to;
-          key[u0 + u] = valid[u0 + u] ? order_key(v[u]) : 0u;
-        }
-      } else {
+        for (int u = 0; u < kU; ++u) key[u0 + u] = order_key(v[u]);
+      }
+    }
+  };
+  // fn(key, row) for this thread's keys.
+  auto each_key = [&](int from, int to, const auto& fn) {
+#pragma unroll
+    for (int u0 = 0; u0 < kRegKeys; u0 += kU) {
+      if (from + u0 * NT < to) {
 #pragma unroll
         for (int u = 0; u < kU; ++u) {
-          valid[u0 + u] = false;
-          key[u0 + u] = 0u;
+          const int j = from + (u0 + u) * NT + tid;
+          if (j < to) fn(key[u0 + u], j);
         }
       }
     }
@@ -267,11 +287,10 @@ __global__ __launch_bounds__(NT) void select_kernel(SelectArgs a) {
         uint32_t km = 0, cn = 0;
         if (regs) {
           load_keys(0, n);
-#pragma unroll
-          for (int u = 0; u < kRegKeys; ++u) {
-            km = max(km, key[u]);  // slots past the rows hold 0
-            cn += valid[u] && key[u] == 0u ? 1u : 0u;
-          }
+          each_key(0, n, [&](uint32_t k, int) {
+            km = max(km, k);
+            cn += k == 0u ? 1u : 0u;
+          });
         } else {
           for (int j = tid; j < n; j += NT) {
             const float v = rank(j);
@@ -289,9 +308,7 @@ __global__ __launch_bounds__(NT) void select_kernel(SelectArgs a) {
         const double dh = (double)head, dt = (double)a.tau;
         uint32_t cn = 0, unused = 0;
         if (regs) {
-#pragma unroll
-          for (int u = 0; u < kRegKeys; ++u)
-            cn += (valid[u] && key[u] != 0u && dt * (double)key_value(key[u]) > dh) ? 1u : 0u;
+          each_key(0, n, [&](uint32_t k, int) { cn += (k != 0u && dt * (double)key_value(k) > dh) ? 1u : 0u; });
         } else {
           for (int j = tid; j < n; j += NT) {
             const float v = rank(j);
@@ -336,9 +353,9 @@ __global__ __launch_bounds__(NT) void select_kernel(SelectArgs a) {
   if (m > 0 && hi - lo <= kRegKeys * NT) {
     if constexpr (!kShrink) load_keys(lo, hi);
     auto count_digits = [&](uint32_t* hist, int shift, uint32_t prefix, uint32_t pmask) {
-#pragma unroll
-      for (int u = 0; u < kRegKeys; ++u)
-        if (valid[u] && (key[u] & pmask) == prefix) atomicAdd(&hist[(key[u] >> shift) & 255u], 1u);
+      each_key(lo, hi, [&](uint32_t k, int) {
+        if ((k & pmask) == prefix) atomicAdd(&hist[(k >> shift) & 255u], 1u);
+      });
     };
     radix_select<NT>(count_digits, (uint32_t)m, sh, &T, &need, &countT);
     if (need == countT) {
@@ -347,14 +364,10 @@ __global__ __launch_bounds__(NT) void select_kernel(SelectArgs a) {
         for (int hh = 0; hh < nheads; ++hh) keep[(long long)hh * c + j] = 1;
       for (int j = max(fr, hi) + tid; j < n; j += NT)
         for (int hh = 0; hh < nheads; ++hh) keep[(long long)hh * c + j] = 1;
-#pragma unroll
-      for (int u = 0; u < kRegKeys; ++u) {
-        const int j = lo + u * NT + tid;
-        if (valid[u]) {
-          const uint8_t kp = (j < fs || j >= fr || key[u] >= T) ? 1 : 0;
-          for (int hh = 0; hh < nheads; ++hh) keep[(long long)hh * c + j] = kp;
-        }
-      }
+      each_key(lo, hi, [&](uint32_t k, int j) {
+        const uint8_t kp = (j < fs || j >= fr || k >= T) ? 1 : 0;
+        for (int hh = 0; hh < nheads; ++hh) keep[(long long)hh * c + j] = kp;
+      });
       return;
     }
   } else if (m > 0) {

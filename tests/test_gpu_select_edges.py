@@ -37,7 +37,9 @@ def test_per_head_slots(kind):
     assert int(c.dev_status[0]) == 0
 
 
-@pytest.mark.parametrize("HK,kind", [(1, "zipf"), (2, "special"), (3, "zipf"), (4, "ties"), (5, "zipf"), (8, "zipf")])
+# Every number of heads in the group of the head sums, and a second group short of a head.
+@pytest.mark.parametrize("HK,kind", [(1, "zipf"), (2, "special"), (3, "zipf"), (4, "ties"), (5, "zipf"), (6, "zipf"),
+                                     (8, "zipf")])
 def test_head_sum_slots(HK, kind):
     note("select edges head sums, HK=%d %s" % (HK, kind))
     lengths = edges(1024)

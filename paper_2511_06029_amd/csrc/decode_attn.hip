@@ -921,8 +921,8 @@ struct BlockPlan {
   bool valid = false;             // the block has a chunk
 };
 
-// Decode blocks the chip holds at once: three on each of 256 CUs.
-constexpr int kResidentBlocks = 768;
+// Decode blocks of two and of three on each of the 256 CUs (the most it holds).
+constexpr int kPairBlocks = 512, kResidentBlocks = 768;
 
 // Hinted steps are capped so that their sum over 1024 sequences stays an int.
 constexpr int kMaxHintSteps = 1 << 20;
@@ -989,21 +989,34 @@ __device__ inline BlockPlan plan_block(const DecodeArgs& a, int blk, SeqWords& w
     // 11.2 us a call; 9 chunks, 8.8 us).
     if (a.adaptive) v = max(v, a.least_steps);
     set_spb(max(v, 1));
-    // Rounding up to whole chunks can pass nb.  Where all nb blocks are
-    // resident at once the few more would share CUs that already hold their
-    // two, and those blocks, and the segments they belong to, end last (520
-    // and 528 blocks: 21 and 38 us where the others were done after 17 and
-    // 30).  Longer chunks until the blocks fit; with at most half as many
-    // segments as blocks that is at most twice the length.  Llama-8B batch 8,
-    // 2300-3100 rows: 26.5 -> 24.0 us a call; Qwen-7B batch 16, 4915-5200
-    // rows: 45.1 -> 38.6 us.
-    if (a.fit && nb <= kResidentBlocks && 2LL * B * a.HK <= nb) {
-      for (;;) {
+    // Rounding up to whole chunks can leave some CUs three blocks where the
+    // others have two; those blocks, and the segments they belong to, end last
+    // (520 and 528 blocks: 21 and 38 us where the others were done after 17 and
+    // 30).  Longer chunks until no CU has more than two, where that keeps seven
+    // tenths of the blocks: three chunks of the old length are then more work
+    // than two of the new (3 n1 / 2 n0 from 1.05 on).  Qwen-7B batch 16,
+    // 4915-5200 rows: 45.1 -> 38.6 us a call; Llama-8B batch 8, 2300-3100 rows:
+    // 26.5 -> 24.0 us.  Of 110 batches of 2 to 60 sequences with 513 to 768
+    // blocks, those that pass gain up to 13% and lose at most 2.2% (median +5%);
+    // of the rest, longer chunks slow 700 or more blocks by up to 14% (22 x 3300
+    // rows, 704 -> 528 blocks) and change three chunks a segment to two by -2%
+    // to +2%.
+    if (a.fit && nb <= kResidentBlocks && (long long)B * a.HK <= kPairBlocks) {
+      auto blocks = [&]() {
         int cnt = 0;
 #pragma unroll
         for (int r = 0; r < R; ++r) cnt += kWave * r + lane < B ? chunks(stp[r]) : 0;
-        if (__builtin_amdgcn_readlane(wave_incl_scan_i32(cnt), kWave - 1) * a.HK <= nb) break;
-        set_spb(spb + 1 + (spb >> 4));
+        return __builtin_amdgcn_readlane(wave_incl_scan_i32(cnt), kWave - 1) * a.HK;
+      };
+      const int n0 = blocks();
+      if (n0 > kPairBlocks && n0 <= kResidentBlocks) {
+        const int spb0 = spb;
+        int n1;
+        do {
+          set_spb(spb + 1 + (spb >> 4));
+          n1 = blocks();
+        } while (n1 > kPairBlocks && 10 * n1 >= 7 * n0);
+        if (10 * n1 < 7 * n0) set_spb(spb0);
       }
     }
   }

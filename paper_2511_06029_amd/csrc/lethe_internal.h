@@ -131,7 +131,7 @@ struct DecodeArgs {
   int32_t min_chunks;    // adaptive split: fewest chunks (at most nbt)
   int32_t least_steps;   // adaptive split: fewest hinted steps per chunk
   int32_t spare_steps;   // adaptive split: steps added to every hint
-  int32_t fit;           // chunks are lengthened until the blocks fit the resident ones
+  int32_t fit;           // chunks may be lengthened so that no CU has three blocks
   int32_t nch_flat;      // chunks per segment when every hint is 0
   int32_t deterministic; // fixed step schedule instead of the per-segment step counter
   // Compacting call only (else null): the plan lethe_kv_compact_plan wrote.

@@ -1,14 +1,17 @@
 """Decode tiling on an MI355X at the edges of its rules, against the oracle:
 segments whose first round of steps covers every row (and the appended one),
 one row or one step more, in both storage types; and batches whose chunks
-rounded up pass the resident blocks, so that the chunks are lengthened.
+rounded up pass two blocks a CU, so that the chunks may be lengthened; and how
+many blocks the split then keeps.
 """
 import numpy as np
 import pytest
+import torch
 
+from paper_2511_06029_amd import lethe as L
 from workloads import synth
 
-from test_gpu_parity import Harness, close
+from test_gpu_parity import DEV, Harness, close
 from test_gpu_tiling import note, ragged, step
 
 pytestmark = pytest.mark.gpu
@@ -48,3 +51,34 @@ def test_chunks_fit_the_resident_blocks(lengths, HK):
         close(out, ref, "step %d" % t)
     H.check_scores(0)
     assert int(H.c.dev_status[0]) == 0
+
+
+def multi_chunk_blocks(lengths, HK, G=2, D=64, spare=40):
+    """Blocks a decode call's split gives segments of more than one chunk: each
+    writes one partial, and no other block writes to the workspace."""
+    c = L.LetheCache(1, [n + spare for n in lengths], G * HK, HK, D, device=DEV)
+    c.k.normal_()
+    c.v.normal_()
+    c.len.copy_(torch.tensor([lengths], dtype=torch.int32))
+    c.flush()
+    q = torch.randn((len(lengths), G * HK, D), device=DEV).to(torch.bfloat16)
+    kn = torch.randn((len(lengths), HK, D), device=DEV).to(torch.bfloat16)
+    ws = c.workspace(L.OP_DECODE)
+    ws.fill_(0xA5)
+    out = torch.zeros(q.shape, device=DEV)
+    L.decode_attn_score(c, 0, q, kn, kn, 0.9, 0.0, out, ws)
+    torch.cuda.synchronize()
+    stride = (4 * G * (D + 2) + 127) // 128 * 128
+    parts = ws[:ws.numel() // stride * stride].view(-1, stride)
+    assert int(c.dev_status[0]) == 0 and bool(torch.isfinite(out).all())
+    return int((parts != 0xA5).any(dim=1).sum())
+
+
+# Lengths and the blocks of their split.  Lengthening would leave 352, 528,
+# 384, 312 and 576 of the first five; the last three pass.
+@pytest.mark.parametrize("lengths,HK,blocks", [([2000] * 22, 8, 528), ([3300] * 22, 8, 704), ([1300] * 48, 4, 576),
+                                               ([513] * 31 + [4097], 8, 592), ([3300] * 24, 8, 768),
+                                               ([2000] * 13, 8, 416), ([2000] * 17, 8, 408), ([5000] * 32, 4, 512)])
+def test_chunks_are_lengthened_only_where_most_blocks_stay(lengths, HK, blocks):
+    note("fit %d sequences of %d to %d rows" % (len(lengths), min(lengths), max(lengths)))
+    assert multi_chunk_blocks(lengths, HK) == blocks

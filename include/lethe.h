@@ -172,10 +172,14 @@ size_t lethe_state_bytes(const lethe_cache* cache);
  * non-zero value every block's steps are fixed and repeated calls are
  * bit-identical (about 3% slower on the Llama-8B batch-128 workload, 5% on
  * the Qwen-7B batch-16 one).  By default a call splits its hinted rows into
- * chunks of about 14 steps, at least min(512, N) and at most N chunks, N
- * being one per 1024 rows of capacity (512 to 4096); LETHE_DECODE_BLOCKS
- * fixes the number of chunks instead, LETHE_DECODE_STEPS_PER_CHUNK and
- * LETHE_DECODE_MIN_CHUNKS change the two defaults.
+ * chunks of about 14 steps, at least min(512, N) and at most N chunks (before
+ * rounding up to whole chunks a segment), N being one per 1024 rows of capacity
+ * (512 to 4096).  bf16 calls take no chunk shorter than four steps (so a short
+ * context has fewer chunks), and longer ones where 513 to 768 chunks can become
+ * at most 512 without losing three tenths of them.  LETHE_DECODE_BLOCKS fixes
+ * the number of chunks instead, LETHE_DECODE_STEPS_PER_CHUNK and
+ * LETHE_DECODE_MIN_CHUNKS change the first two numbers; with any of the three
+ * set the two bf16 rules are off.
  * Accumulation is fp32; results match the exact result to about 1e-5
  * relative.  Errors: LETHE_ERR_INVALID (null pointer, layer out of range,
  * gamma outside (0, 1] or NaN, NaN scale), LETHE_ERR_UNSUPPORTED,

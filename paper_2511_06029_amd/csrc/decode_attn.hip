@@ -903,8 +903,11 @@ struct AttnLds<float, D> {
 // same values): with S the hinted steps of all segments and nb the chunks
 // the call aims for (S / steps_per_chunk between min(min_chunks, nbt) and
 // nbt, or nbt itself when the target is fixed), a segment of w hinted steps
-// gets nch = clamp(ceil(w / ceil(S / nb)), 1, kMaxChunksPerSeg) chunks, one
-// block each.  The blocks of sequence b are consecutive, KV head by KV head:
+// gets nch = clamp(ceil(w / spb), 1, kMaxChunksPerSeg) chunks of spb =
+// ceil(S / nb) steps, one block each.  bf16 calls without a setting of the
+// environment count one spare step on every hint, take at least least_steps
+// steps a chunk, and may lengthen the chunks so that no CU holds three blocks
+// (fit).  The blocks of sequence b are consecutive, KV head by KV head:
 // block P_b + h nch_b + c is chunk c of segment (b, h).  When every hint is 0
 // each segment gets nch_flat chunks.  A hint only shapes the split: every
 // chunk count covers the segment's actual rows.  Blocks past the last chunk
@@ -987,8 +990,7 @@ __device__ inline BlockPlan plan_block(const DecodeArgs& a, int blk, SeqWords& w
     // A chunk of fewer steps than wavefronts adds a partial and no loads (one
     // sequence of 1111 rows: 35 chunks a segment, combined in three batches,
     // 11.2 us a call; 9 chunks, 8.8 us).
-    if (a.adaptive) v = max(v, a.least_steps);
-    set_spb(max(v, 1));
+    set_spb(max(v, a.least_steps));
     // Rounding up to whole chunks can leave some CUs three blocks where the
     // others have two; those blocks, and the segments they belong to, end last
     // (520 and 528 blocks: 21 and 38 us where the others were done after 17 and
@@ -1565,10 +1567,12 @@ lethe_status launch_tdg(const DecodeArgs& a_in, hipStream_t s) {
   // gains until its next hint, so that a short segment's first round still
   // covers it (two sequences of 619 to 688 rows, 2 KV heads: 11.4 us a call;
   // 12.1 without, where 20 waves take a second round for the last rows).  fp32
-  // steps and sums are shorter and keep the split they had.
-  a.least_steps = sizeof(T) == 2 ? kNumWaves : 1;
-  a.spare_steps = sizeof(T) == 2 && a.adaptive ? 1 : 0;
-  a.fit = sizeof(T) == 2;
+  // steps and sums are shorter and keep the split they had, and a split that
+  // the environment sets is taken as it is.
+  const bool tune = sizeof(T) == 2 && env_blocks <= 0 && env_spc <= 0 && env_minc <= 0;
+  a.least_steps = tune ? kNumWaves : 1;
+  a.spare_steps = tune ? 1 : 0;
+  a.fit = tune;
   const int64_t segs = (int64_t)a.B * a.HK;
   // Flat split (no hints yet): at least four chunks per segment, so that with
   // many segments of ragged lengths the dispatcher hands the slots of early

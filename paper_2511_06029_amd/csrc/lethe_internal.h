@@ -129,8 +129,8 @@ struct DecodeArgs {
   int32_t adaptive;      // fewer chunks for small hinted totals
   int32_t steps_per_chunk; // adaptive split: hinted steps a chunk aims for
   int32_t min_chunks;    // adaptive split: fewest chunks (at most nbt)
-  int32_t least_steps;   // adaptive split: fewest hinted steps per chunk
-  int32_t spare_steps;   // adaptive split: steps added to every hint
+  int32_t least_steps;   // fewest hinted steps per chunk
+  int32_t spare_steps;   // steps added to every hint
   int32_t fit;           // chunks may be lengthened so that no CU has three blocks
   int32_t nch_flat;      // chunks per segment when every hint is 0
   int32_t deterministic; // fixed step schedule instead of the per-segment step counter

@@ -82,3 +82,23 @@ def multi_chunk_blocks(lengths, HK, G=2, D=64, spare=40):
 def test_chunks_are_lengthened_only_where_most_blocks_stay(lengths, HK, blocks):
     note("fit %d sequences of %d to %d rows" % (len(lengths), min(lengths), max(lengths)))
     assert multi_chunk_blocks(lengths, HK) == blocks
+
+
+# Steps of 32 rows: 63 a segment.  The default split has 32, 64 and 416 blocks.
+@pytest.mark.parametrize("env,lengths,HK,blocks", [
+    ({"LETHE_DECODE_STEPS_PER_CHUNK": "1"}, [2000], 2, 126),   # one step a chunk
+    ({"LETHE_DECODE_MIN_CHUNKS": "512"}, [2000], 2, 126),
+    ({"LETHE_DECODE_STEPS_PER_CHUNK": "2", "LETHE_DECODE_MIN_CHUNKS": "1"}, [2000] * 2, 2, 128),  # two
+    ({"LETHE_DECODE_BLOCKS": "512"}, [2000] * 13, 8, 520),     # 512, and one more for some segments
+])
+def test_settings_of_the_environment_are_taken_as_they_are(env, lengths, HK, blocks, monkeypatch):
+    for k, v in env.items():
+        monkeypatch.setenv(k, v)
+    note("split by %s" % env)
+    assert multi_chunk_blocks(lengths, HK) == blocks
+
+
+@pytest.mark.parametrize("lengths,HK,blocks", [([2000], 2, 32), ([2000] * 2, 2, 64), ([130], 1, 2)])
+def test_default_chunks_have_four_steps(lengths, HK, blocks):
+    note("default split of %s" % lengths)
+    assert multi_chunk_blocks(lengths, HK) == blocks

@@ -396,7 +396,8 @@ lethe_status lethe_segmented_shrink(const lethe_cache* c, int32_t segments, floa
 
 size_t lethe_prefill_workspace_bytes(const lethe_cache* c, int64_t q_rows) {
   if (!c || q_rows <= 0 || c->num_q_heads <= 0) return 0;
-  // (max, 1 / sum) per query row and head, plus slack for reads in pairs.
+  // (max, 1 / sum) per query row and head; the 16 bytes more are not read (the
+  // size that callers have allocated is kept).
   return align_up((size_t)q_rows * (size_t)c->num_q_heads * 2 * sizeof(float) + 16, 256);
 }
 

@@ -67,15 +67,10 @@ struct PfCfg {
   static constexpr int VBLK = kWave * 16 + 64;
   static constexpr int VTILE = VLOADS * VBLK;
   static __device__ constexpr int vaddr(int r, int c) { return (r % VLOADS) * VBLK + (r / VLOADS) * ROWB + c; }
-  static constexpr int BUF = KTILE + VTILE;
 };
 
-// s_waitcnt with only a vector-memory count (expcnt and lgkmcnt left free).
-template <int N>
-__device__ inline void wait_vmcnt() {
-  static_assert(N >= 0 && N < 64, "vmcnt range");
-  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
-}
+// Waits for every vector-memory load (expcnt and lgkmcnt left free).
+__device__ inline void wait_vmem() { __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8)); }
 
 __device__ inline pf_bf16x8_t pf_zero8() {
   pf_bf16x8_t z;
@@ -129,6 +124,9 @@ __device__ inline bool pf_seq(const PrefillArgs& a, int b, int h, PfSeq& sq) {
 // resident blocks, so a long sequence's blocks must not start last (four
 // chunks of about 1000 queries over 3001 to 12000 keys: 1012 us a call in unit
 // order, 811 us in this one; finding the block takes ten rounds of a wave sum).
+// More than 64 sequences, which a wave's lanes cannot hold, keep unit order
+// (chunks of 300 queries over 305 to 2948 keys, 4 KV heads: 64 sequences 429 us
+// in this order, 66 in unit order 473, 7% more a sequence).
 template <int G>
 __device__ inline bool pf_block(const PrefillArgs& a, int& b, int& h, int& ub) {
   const int segs = a.B * a.HK;
@@ -149,7 +147,7 @@ __device__ inline bool pf_block(const PrefillArgs& a, int& b, int& h, int& ub) {
         if (x == 0) return nb;
         if (!work || lane >= a.B || (n - 1) / 32 < x) return 0;
         const int t = max(0, 32 * x - (n - qlen)) / 32;
-        return nb - max(0, t * G) / kPfWaves;
+        return nb - t * G / kPfWaves;
       };
       auto total = [&](int v) { return __builtin_amdgcn_readlane(wave_incl_scan_i32(v), kWave - 1) * a.HK; };
       if (idx >= total(nb)) return false;
@@ -449,7 +447,7 @@ __global__ __launch_bounds__(kPfThreads) __attribute__((amdgpu_waves_per_eu(2)))
   // (the barrier alone would not); the barrier then makes every wave's visible
   // and guarantees that the buffers to fill have been read by all.
   auto advance = [&](int st, char* kfill, char* vfill) {
-    wait_vmcnt<0>();
+    wait_vmem();
     __syncthreads();
     issue_k(st + 2, kfill);
     issue_v(st + 1, vfill);
@@ -457,7 +455,7 @@ __global__ __launch_bounds__(kPfThreads) __attribute__((amdgpu_waves_per_eu(2)))
   issue_k(0, ktile0);
   issue_k(1, ktile1);
   issue_v(0, vtile0);
-  wait_vmcnt<0>();
+  wait_vmem();
   __syncthreads();
   const int own = (kend + STEP - 1) / STEP;  // steps of this wave
   clear(sa);
@@ -626,13 +624,13 @@ __global__ __launch_bounds__(kWave * KW * IG) __attribute__((amdgpu_waves_per_eu
   issue(ig, buf0);
   const int rounds = (nitems + IG - 1) / IG;
   for (int x = 0; x < rounds; x += 2) {
-    wait_vmcnt<0>();
+    wait_vmem();
     __syncthreads();
     float2 qs = st_next;
     issue((x + 1) * IG + ig, buf1);
     compute(x * IG + ig, buf0, qs);
     if (x + 1 >= rounds) break;
-    wait_vmcnt<0>();
+    wait_vmem();
     __syncthreads();
     qs = st_next;
     issue((x + 2) * IG + ig, buf0);
@@ -700,9 +698,13 @@ lethe_status launch_prefill_dg(const PrefillArgs& args, hipStream_t s) {
   const long long wide = segs * ((a.max_kv + 127LL) / 128);
   if (wide == 0 || fwd_blocks == 0) return LETHE_OK;
   // 128 keys a block where those blocks fill the chip's 256 CUs, else 64 keys
-  // and eight item groups (24 segments of 77 to 421 rows: 12 us against 64 us
-  // with 256 keys a block).  At batch 8 and 2048 rows 128 keys in 8 waves take
-  // 2% less than 256 keys, 4% less than 64.
+  // and eight item groups, one block a CU (24 segments of 77 to 421 rows: 12 us
+  // against 64 us with 256 keys a block).  Whole calls, 64 against 128 keys:
+  // prompts of 1000 to 3000 rows, 64 to 192 blocks of 128, 28 to 22% less; 256
+  // blocks 5 to 20% less (the first keys meet every query, and their blocks
+  // last); 512 and 1024 blocks 7 to 12% more.  Chunks of 200 queries, whose
+  // blocks are alike: 64 and 96 blocks 8 to 9% less, 136 alike, 160 to 256 5 to
+  // 12% more, 1024 29% more.  The line lies between the two.
   if (wide >= 256) return launch_score<D, G, 1, 4, 2>(a, (unsigned)segs, s);
   return launch_score<D, G, 1, 2, 8>(a, (unsigned)segs, s);
 }

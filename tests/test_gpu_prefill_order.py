@@ -40,6 +40,19 @@ def test_blocks_over_all_sequences(G, HK, lengths, qlens):
     cs.check(heads=[0, HK - 1])
 
 
+# One lane a sequence: 64 are ordered, 65 keep unit order (1280 and more blocks).
+@pytest.mark.parametrize("D,G,nseq", [(64, 2, 64), (64, 2, 65), (128, 3, 64)])
+def test_most_sequences_of_an_ordered_batch(D, G, nseq):
+    note("prefill order, %d sequences, D=%d" % (nseq, D))
+    lengths = [1 + (53 * b) % 300 for b in range(nseq)]
+    lengths[7] = 301
+    qlens = [n if b % 3 else max(0, n - 40) for b, n in enumerate(lengths)]
+    cs = Case(D, G, 4, lengths, qlens, seed=nseq + D)
+    cs.run()
+    assert np.all(np.isfinite(f32(cs.out)))
+    cs.check(seqs=[0, 1, 6, 7, 31, 62, nseq - 1], heads=[0, 3])
+
+
 def test_flagged_sequences_in_an_ordered_batch():
     lengths, qlens = [700, 64, 300, 512, 33, 200], [700, 64, 300, 512, 33, 200]
     note("prefill order, flagged")

@@ -177,15 +177,17 @@ __device__ inline bool pf_block(const PrefillArgs& a, int& b, int& h, int& ub) {
   return true;
 }
 
-// Bound by the matrix cores at the clock the power limit leaves them: at
-// batch 8, 2048 tokens, Llama-8B heads, both passes do 550 GFLOP (P V in two
-// halves, S^T again in pass 2) in 0.61 ms, 0.90 PFLOP/s, where an 8192^3 bf16
-// library product reaches 1.13 to 1.23 on the same data distribution (zeros
-// in place of the data: 0.50 ms and 1.70).  16x16x32 products with 32-key
-// steps took 0.81 ms: twice the LDS reads and softmax instructions a flop,
-// and a tile's four waves idled where a group has fewer heads.  The V blocks'
-// 64 bytes of padding make its reads free of bank conflicts (32 bytes: a
-// third of the LDS cycles); two blocks of up to 256 registers a lane fit a CU.
+// Bound by a SIMD's issue of both units, at a clock that power lowers: at batch
+// 8, 2048 tokens, Llama-8B heads, the matrix cores are busy 46% and the vector
+// units 50% of the time, next to no time both (two waves a SIMD); both passes do
+// 550 GFLOP (P V in two halves, S^T again in pass 2) in 0.62 ms, 0.89 PFLOP/s,
+// where an 8192^3 bf16 library product reaches 1.13 to 1.23 on the same data
+// distribution (zeros in place of the data: 0.50 ms and 1.70).  16x16x32
+// products with 32-key steps took 0.81 ms: twice the LDS reads and softmax
+// instructions a flop, and a tile's four waves idled where a group has fewer
+// heads.  The V blocks' 64 bytes of padding leave no bank conflicts (with 32
+// bytes they take a third of the LDS cycles); two blocks of up to 256 registers
+// a lane fit a CU.
 template <int D, int G>
 __global__ __launch_bounds__(kPfThreads) __attribute__((amdgpu_waves_per_eu(2))) void prefill_fwd_kernel(PrefillArgs a) {
   using Cfg = PfCfg<D>;
@@ -512,8 +514,9 @@ __global__ __launch_bounds__(kPfThreads) __attribute__((amdgpu_waves_per_eu(2)))
 // takes the work items (tile of 32 queries, head) ig, ig + IG, ... and keeps
 // its own double-buffered query tile.  A weight costs a multiply-add, an exp2
 // and a multiply-add against 16 matrix-core cycles a lane, so the pass needs
-// waves to overlap the two: 32 keys a wave hold 112 registers, four waves a
-// SIMD, where 64 keys held 190.
+// waves to overlap the two: 32 keys a wave hold 116 registers, four waves a
+// SIMD, where 64 keys held 190.  At batch 8, 2048 tokens it takes 0.18 ms, the
+// vector units busy 59% and the matrix cores 35% of it.
 template <int D, int G, int NS, int KW, int IG>
 __global__ __launch_bounds__(kWave * KW * IG) __attribute__((amdgpu_waves_per_eu(KW * IG / 4))) void
     prefill_score_kernel(PrefillArgs a) {

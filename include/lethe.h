@@ -449,8 +449,9 @@ lethe_status lethe_kv_compact_layers(const lethe_cache* cache, int32_t layer_beg
  * after the layer's last change; between the plan and the last of those
  * calls only these calls may touch the plan (they set its step flags).
  *
- * The work split is lethe_decode_attn_score's: the wavefronts of a segment
- * take its 32-row steps in increasing order.  From the first step holding
+ * The work split is lethe_decode_attn_score's, with the rows the plan was made
+ * for in place of the hints: the wavefronts of a segment take its 32-row steps
+ * in increasing order.  From the first step holding
  * an evicted row on, a wavefront marks its step read as soon as the step's
  * loads have landed, and before storing the step's kept rows at their new
  * places (at or before their old ones) waits for the steps those places lie

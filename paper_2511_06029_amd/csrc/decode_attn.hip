@@ -908,10 +908,14 @@ struct AttnLds<float, D> {
 // environment count one spare step on every hint, take at least least_steps
 // steps a chunk, and may lengthen the chunks so that no CU holds three blocks
 // (fit).  The blocks of sequence b are consecutive, KV head by KV head:
-// block P_b + h nch_b + c is chunk c of segment (b, h).  When every hint is 0
-// each segment gets nch_flat chunks.  A hint only shapes the split: every
-// chunk count covers the segment's actual rows.  Blocks past the last chunk
-// have nothing to do.
+// block P_b + h nch_b + c is chunk c of segment (b, h).  A compacting call
+// takes the live rows its plan was made for in place of the hints, which then
+// hold the rows kept: it reads them all (one sequence of 1111 rows, 40% kept,
+// eight layers and their plan: 177 us split by the rows kept, 119 us so; the
+// lengths themselves change during the launch).  When every hint is 0 each
+// segment gets nch_flat chunks.  A hint only shapes the split: every chunk
+// count covers the segment's actual rows.  Blocks past the last chunk have
+// nothing to do.
 struct SeqWords {
   int n, cp;           // len and cap
   long long sbase;     // seq_base
@@ -933,7 +937,7 @@ constexpr int kMaxHintSteps = 1 << 20;
 // The plan of block `blk` from R rows of 64 sequences (sequence 64 r + lane).
 // With kWords the sequences' own words come in the same round trip and the
 // chosen one's are returned in `w` (R = 4 covers up to 256 sequences).
-template <int R, bool kWords>
+template <int R, bool kWords, bool kCompact>
 __device__ inline BlockPlan plan_block(const DecodeArgs& a, int blk, SeqWords& w) {
   const int lane = threadIdx.x & (kWave - 1);
   const int B = a.B;
@@ -944,7 +948,7 @@ __device__ inline BlockPlan plan_block(const DecodeArgs& a, int blk, SeqWords& w
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     const int bb = min(kWave * r + lane, B - 1);  // clamped: every load is issued
-    hv[r] = a.hint[bb];
+    hv[r] = kCompact ? min(a.seg_plan[(long long)bb * a.HK * kSegPlanWords], 32 * kMaxHintSteps) : a.hint[bb];
     if constexpr (kWords) {
       wn[r] = a.len[bb];
       wc[r] = a.cap[bb];
@@ -1069,13 +1073,13 @@ __device__ inline void decode_body(const DecodeArgs& a) {
   SeqWords sw;
   BlockPlan bp;
   if (a.B <= kWave) {
-    bp = plan_block<1, true>(a, blk, sw);
+    bp = plan_block<1, true, kCompact>(a, blk, sw);
   } else if (a.B <= 2 * kWave) {
-    bp = plan_block<2, true>(a, blk, sw);
+    bp = plan_block<2, true, kCompact>(a, blk, sw);
   } else if (a.B <= 4 * kWave) {
-    bp = plan_block<4, true>(a, blk, sw);
+    bp = plan_block<4, true, kCompact>(a, blk, sw);
   } else {
-    bp = plan_block<kMaxSeqs / kWave, false>(a, blk, sw);
+    bp = plan_block<kMaxSeqs / kWave, false, kCompact>(a, blk, sw);
     if (bp.valid) {
       const int bb = bp.b;
       sw.n = a.len[bb];

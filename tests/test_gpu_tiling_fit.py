@@ -102,3 +102,35 @@ def test_settings_of_the_environment_are_taken_as_they_are(env, lengths, HK, blo
 def test_default_chunks_have_four_steps(lengths, HK, blocks):
     note("default split of %s" % lengths)
     assert multi_chunk_blocks(lengths, HK) == blocks
+
+
+@pytest.mark.parametrize("lengths,HK,frac,blocks", [([2000], 2, 0.4, 32), ([2000], 2, 1.0, 32), ([1300] * 2, 3, 0.1, 66)])
+def test_compacting_call_is_split_by_the_rows_it_reads(lengths, HK, frac, blocks):
+    """Four 32-row steps a chunk (63 and 41 steps and the spare one), whatever
+    the plan keeps; a segment's row count after the call is what it keeps."""
+    note("compacting call, %.0f%% of %s" % (100 * frac, lengths))
+    D, G = 64, 2
+    c = L.LetheCache(1, [n + 40 for n in lengths], G * HK, HK, D, device=DEV)
+    c.k.normal_()
+    c.v.normal_()
+    c.len.copy_(torch.tensor([lengths], dtype=torch.int32))
+    c.flush()
+    keep = torch.zeros((1, c.rows_per_layer), dtype=torch.uint8, device=DEV)
+    kept = [int(frac * n) for n in lengths]
+    for b, n in enumerate(lengths):
+        for h in range(HK):
+            r0, _ = c.seg_rows(b, h)
+            keep[0, r0 + n - kept[b]:r0 + n] = 1
+    plan, ws = c.workspace(L.OP_COMPACT_PLAN), c.workspace(L.OP_DECODE)
+    L.kv_compact_plan(c, keep, plan)
+    ws.fill_(0xA5)
+    q = torch.randn((len(lengths), G * HK, D), device=DEV).to(torch.bfloat16)
+    kn = torch.randn((len(lengths), HK, D), device=DEV).to(torch.bfloat16)
+    out = torch.zeros(q.shape, device=DEV)
+    L.decode_attn_score_compact(c, 0, q, kn, kn, 0.9, 0.0, out, plan, ws)
+    torch.cuda.synchronize()
+    stride = (4 * G * (D + 2) + 127) // 128 * 128
+    parts = ws[:ws.numel() // stride * stride].view(-1, stride)
+    assert int(c.dev_status[0]) == 0 and bool(torch.isfinite(out).all())
+    assert c.len[0].tolist() == [k + 1 for k in kept]
+    assert int((parts != 0xA5).any(dim=1).sum()) == blocks
